@@ -11,14 +11,18 @@
 // fragment reads (32 rows at one chunk) hit distinct banks.  Rows past M or N read the last row
 // and are not stored.
 //
-// linear_kernel (any K, N multiple of 8): 4 waves, a 128 x 128 tile of y^T, two work-groups per
-// compute unit, wave w owning a 64 x 64 quarter as 2 x 2 blocks.  The k steps are double
-// buffered: the global loads of step s + 1 are in flight in registers while step s is
-// multiplied, then written to the other LDS buffer before the step's one barrier.  Chunks past
-// K read as zeros.
+// linear_kernel_pc (every K up to 2^22): four waves multiply, four load straight into an LDS ring; four
+// tile sizes, chosen by a cost rule in launch_linear.
 //
-// linear_kernel_big (K a multiple of 64, the model's case): below.
+// linear_kernel (longer rows, whose tiles 32-bit offsets cannot address): 4 waves, a 128 x 128 tile
+// of y^T, two work-groups per compute unit, wave w owning a 64 x 64 quarter as 2 x 2 blocks.  The k
+// steps are double buffered: the global loads of step s + 1 are in flight in registers while step
+// s is multiplied, then written to the other LDS buffer before the step's one barrier.  Chunks
+// past K read as zeros.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cmath>
 
 #include "kernels.hpp"
 
@@ -170,143 +174,242 @@ __global__ __launch_bounds__(kThreads, 2) void linear_kernel(LinearArgs a) {
   }
 }
 
-// ---- K a multiple of 64: direct-to-LDS staging, a three-stage ring, larger tiles ----------------
+// ---- direct-to-LDS staging: waves 0-3 multiply, waves 4-7 load ------------------------------------
 //
-// Work-group: 8 waves, a 128 (n) x 256 (m) tile of y^T.  Waves 0-3 (one per SIMD) multiply: wave
-// w owns 64 n (w / 2) x 128 m (w % 2) as 2 x 4 blocks, so a 16-wide k step reads 6 fragments for
-// 8 MFMAs.  Waves 4-7 only load: a stage is the 64-wide k step of both tiles (W 128 rows + x 256
-// rows of 128 bytes, 48 KB), brought straight from global memory into LDS by
-// global_load_lds_dwordx4 (each loader 12 loads of 1 KB = 8 rows): lane l lands in row l / 8,
-// physical chunk l % 8, so it fetches logical chunk (l % 8) ^ swz(row).  Loaders issue stage
-// s + 2 while stage s is multiplied and wait for stage s + 1 before the barrier that ends the
-// step, which also frees stage s's ring slot; issuing a direct-to-LDS load stalls the issuing
-// wave, so keeping the loads off the multiplying waves keeps their MFMA stream going.  After the
-// k loop the multiplying waves add the bias (loaded before the loop) and write the rounded tile
-// into the then free ring, and all 8 waves store it in 16-byte pieces that cover whole row runs
-// (each lane's own results are 8-byte pieces of 32 different rows, which stored directly made
-// every store instruction touch 32 partial cache lines).
-constexpr int kBigBM = 256;
-constexpr int kBigStages = 3;
-constexpr int kWBytes = kBN * kRowBytes;                  // 16 KB
-constexpr int kXBytes = kBigBM * kRowBytes;               // 32 KB
-constexpr int kStageBytes = kWBytes + kXBytes;            // 48 KB
-constexpr int kLoadsPerWave = kStageBytes / 1024 / 4;     // 12
-static_assert(kLoadsPerWave == 12, "vmcnt immediates assume 12 loads per wave per stage");
-
-typedef __attribute__((address_space(1))) void global_void_t;
-
-__device__ __forceinline__ void big_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
-// Load j (0..11) of loader `wave` (0..3) for the stage at k0 into LDS stage address `stage`:
-// loads 0-3 are W rows 32 wave + 8 j .. + 7, loads 4-11 x rows 64 wave + 8 (j - 4) .. + 7.
-__device__ __forceinline__ void big_load(const LinearArgs& a, uint32_t stage, int wave, int lane, int j, int32_t n0,
-                                         int32_t m0, int32_t k0) {
-  const bool is_w = j < 4;
-  const int row = is_w ? 32 * wave + 8 * j + (lane >> 3) : 64 * wave + 8 * (j - 4) + (lane >> 3);
-  const int chunk = (lane & 7) ^ swz(row);
-  // rows past N or M read the last row (finite values; those outputs are not stored)
-  const int32_t r = is_w ? min(n0 + row, a.N - 1) - n0 : min(m0 + row, a.M - 1) - m0;
-  const uint16_t* base = is_w ? a.w + int64_t(n0) * a.K : a.x + int64_t(m0) * a.K;
-  const uint32_t off = uint32_t(r) * uint32_t(a.K) * 2u + uint32_t(k0) * 2u + uint32_t(chunk) * 16u;
-  const uint32_t m0addr = stage + (is_w ? 0 : kWBytes) + (is_w ? 32 * wave + 8 * j : 64 * wave + 8 * (j - 4)) * kRowBytes;
-  // `base` is computed by the scalar unit: an SGPR written by a VALU instruction would need 5 wait
-  // states before this load, which the compiler does not insert ahead of inline assembly
-  asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(m0addr) : "memory");
-}
-
-__device__ __forceinline__ void wait_loads(bool next_in_flight) {
-  if (next_in_flight)
-    asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
-  else
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-}
-
-// Fragment i of the 16-wide k step kk of the stage at LDS offset cur: i < 2 the W block nb = i,
-// else the x block mb = i - 2 (blocks are 32 rows = 4096 bytes apart).
-__device__ __forceinline__ bf16x8_t frag(const uint32_t (&w_off)[4], const uint32_t (&x_off)[4], uint32_t cur, int kk,
-                                         int i) {
-  const uint32_t addr = i < 2 ? w_off[kk] + cur + i * 32 * kRowBytes : x_off[kk] + cur + (i - 2) * 32 * kRowBytes;
-  return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const lds_u32x4_t*>(uintptr_t(addr)));
-}
+// Multiplying wave w (one per SIMD) owns a quarter of the tile (n half w / 2, m half w % 2) as
+// NB x MB blocks of 32 x 32.  The loading waves bring a stage, the 64-wide k step of both operands
+// (W rows, then x rows, 128 bytes each), from global memory into the ring with
+// global_load_lds_dwordx4: a load is 1 KB = 8 rows, lane l lands in row l / 8, physical chunk l % 8,
+// so it fetches logical chunk (l % 8) ^ swz(row).  Issuing such a load stalls the issuing wave, so
+// keeping the loads off the multiplying waves keeps their MFMA stream going.  When K is no multiple
+// of 64 the last stage is read through a buffer descriptor and the chunks past K take an offset
+// outside it, which reads as zero.
+//
+// What bounds it: the stream of operands into LDS.  One compute unit draws at most ~105 GB/s (about
+// 46 bytes per clock) however few of them run, and all together ~12 TB/s with the two larger tiles,
+// 15 with 64 x 128 and 19 with 64 x 64 (two work-groups per unit).  So a launch wants the largest
+// tile that still gives every compute unit one, and a small launch wants small tiles: many units
+// drawing at once, each with a deep ring (several stages in flight hide the ~1 us that a first
+// touch takes).  Measured (us, against a 128 x 256 tile for K a multiple of 64 and linear_kernel
+// otherwise): [1560, 1536] x [1536, 1536]^T 18.1 -> 13.3 (156 tiles of 128 x 128); [72, 1536] x
+// [1536, 1536]^T 16.0 -> 6.7; [1365, 1032] x [1000, 1032]^T 26.7 -> 10.4; [64, 12288] x
+// [1536, 12288]^T 102 -> 36.
+//
+// Two barrier placements.  Mid: the work-group's barrier of stage s comes before its last 16-wide k
+// step; past it stage s + 1 has landed, so its first fragments are read during that k step and the
+// MFMA stream does not wait for LDS at the stage's edge, but a slot is refilled one barrier later
+// and the ring holds one stage less in flight.  Otherwise: the barrier follows the stage's last
+// MFMAs.  With three 48 KB stages the deeper prefetch is worth more ([4680, 1536] x [1536, 1536]^T:
+// 24.4 us against 26.4 with Mid); the smaller tiles have five or more stages and take Mid.
+typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) bf16x4_t lds_bf16x4_t;
 
 constexpr int kPCThreads = 512;
-// output staging after the k loop: the 256 x 128 bf16 tile in LDS rows of 272 bytes (16-byte
-// aligned; consecutive rows start 4 banks apart, so the multiplying waves' 8-byte writes of 32
-// rows at one column conflict at most 2-way)
-constexpr int kYPitch = 272;
-static_assert(kBigBM * kYPitch <= kBigStages * kStageBytes, "the y tile must fit the LDS ring");
 
-// The multiplying waves of linear_kernel_big: the k loop over the LDS ring, then the tile, bias
-// added in float32 and rounded once, written to LDS rows of kYPitch bytes.
-__device__ __forceinline__ void multiply(const LinearArgs& a, uint32_t lds0, int lw, int lane, int32_t n0,
-                                         int32_t m0, int32_t steps) {
+// A kBN (W rows) x kBM (x rows) tile, a ring of kSt stages.
+template <int kBN_, int kBM_, int kSt_, bool kMid_>
+struct Tile {
+  static constexpr int BN = kBN_, BM = kBM_, BK = kBK, St = kSt_;
+  static constexpr bool Mid = kMid_;                       // barrier before a stage's last k step (else after it)
+  static constexpr int Row = BK * 2;                       // bytes of a tile row
+  static constexpr int Chunks = Row / 16;
+  static constexpr int Stage = (BN + BM) * Row;            // W rows, then x rows
+  static constexpr int RowsPerLoad = 1024 / Row;           // rows of one load instruction of a wave
+  static constexpr int WLoads = BN / RowsPerLoad / 4;      // per loader wave and stage
+  static constexpr int XLoads = BM / RowsPerLoad / 4;
+  static constexpr int Loads = WLoads + XLoads;
+  static constexpr int NB = BN / 64, MB = BM / 64;         // 32 x 32 blocks per multiplying wave
+  static constexpr int KK = BK / 16;                       // MFMA k steps per stage
+  static constexpr int YPitch = BN * 2 + 16;               // y staging rows
+  static constexpr int Lds = St * Stage;
+  static_assert(BM * YPitch <= Lds && Lds <= 160 * 1024, "LDS");
+  static_assert((St - 3) * Loads < 63, "vmcnt range");
+};
+
+// Workgroup barrier; at most kLeft of this wave's LDS reads are still in flight.
+template <int kLeft>
+__device__ __forceinline__ void big_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(%0)\n\ts_barrier" ::"n"(kLeft) : "memory");
+}
+
+// Wait until at most n (0 .. kMax) stages of kL loads are in flight.
+template <int kL, int kMax>
+__device__ __forceinline__ void wait_stages(int n) {
+  if constexpr (kMax > 0) {
+    if (n < kMax) {
+      wait_stages<kL, kMax - 1>(n);
+      return;
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kL * kMax) : "memory");
+}
+
+// A loader wave's view of its share of a stage.
+template <class T>
+struct Loader {
+  const uint16_t* w;           // first tile row of W and of x, at k of the next stage
+  const uint16_t* x;
+  uint32_t wbytes, xbytes;     // from there to the end of the tile's last row
+  uint32_t off[T::Loads];      // the lane's byte offset, per load; rows past the matrix read its last row
+  int32_t kc[T::Loads];        // k of the lane's chunk within the stage
+  uint32_t ldsw, ldsx;         // LDS address of this wave's first W and x row in stage 0
+};
+
+// The next stage into ring slot `slot`.  The loads' scalar bases must come from the scalar unit: an
+// SGPR written by a VALU instruction would need 5 wait states before a vector-memory read of it,
+// which the compiler does not insert ahead of inline assembly.  (An M0 write needs one.)
+template <class T>
+__device__ __forceinline__ void load_stage(Loader<T>& l, int slot, int32_t k0, int32_t K) {
+  const uint32_t dw = l.ldsw + slot * T::Stage, dx = l.ldsx + slot * T::Stage;
+  if (k0 + T::BK <= K) {
+#pragma unroll
+    for (int j = 0; j < T::Loads; ++j) {
+      const uint32_t m0 = j < T::WLoads ? dw + j * 1024 : dx + (j - T::WLoads) * 1024;
+      asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(l.off[j]), "s"(j < T::WLoads ? l.w : l.x), "{m0}"(m0) : "memory");
+    }
+  } else {
+    // the last stage when K is no multiple of BK: chunks past K take an offset outside the buffer,
+    // which reads as zero
+#pragma unroll
+    for (int j = 0; j < T::Loads; ++j) {
+      const bool is_w = j < T::WLoads;
+      const uint64_t base = uint64_t(uintptr_t(is_w ? l.w : l.x));
+      const u32x4_t rsrc = {uint32_t(base), uint32_t(base >> 32), is_w ? l.wbytes : l.xbytes, 0x00020000u};
+      const uint32_t m0 = is_w ? dw + j * 1024 : dx + (j - T::WLoads) * 1024;
+      const uint32_t off = k0 + l.kc[j] < K ? l.off[j] : 0x80000000u;
+      asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(off), "s"(rsrc), "{m0}"(m0) : "memory");
+    }
+  }
+  l.w += T::BK;
+  l.x += T::BK;
+  l.wbytes -= T::Row;
+  l.xbytes -= T::Row;
+}
+
+template <class T>
+__device__ __forceinline__ void load_loop(const LinearArgs& a, uint32_t lds0, int lw, int lane, int32_t n0, int32_t m0, int32_t steps) {
+  const int32_t wrows = min(a.N - n0, T::BN), xrows = min(a.M - m0, T::BM);
+  Loader<T> l;
+  l.w = a.w + int64_t(n0) * a.K;
+  l.x = a.x + int64_t(m0) * a.K;
+  l.wbytes = uint32_t(wrows) * uint32_t(a.K) * 2u;
+  l.xbytes = uint32_t(xrows) * uint32_t(a.K) * 2u;
+#pragma unroll
+  for (int j = 0; j < T::Loads; ++j) {
+    const bool is_w = j < T::WLoads;
+    const int row = (is_w ? lw * T::WLoads + j : lw * T::XLoads + j - T::WLoads) * T::RowsPerLoad + lane / T::Chunks;
+    const int chunk = (lane % T::Chunks) ^ swz(row);
+    l.off[j] = uint32_t(min(row, (is_w ? wrows : xrows) - 1)) * uint32_t(a.K) * 2u + uint32_t(chunk) * 16u;
+    l.kc[j] = chunk * 8;
+  }
+  l.ldsw = lds0 + lw * T::WLoads * 1024;
+  l.ldsx = lds0 + T::BN * T::Row + lw * T::XLoads * 1024;
+#pragma unroll
+  for (int t = 0; t < T::St - 1; ++t)
+    if (t < steps) load_stage<T>(l, t, t * T::BK, a.K);
+  wait_stages<T::Loads, T::St - 2>(min(T::St - 1, steps) - 1);
+  big_barrier<0>();                            // stage 0 has landed
+  int slot = T::St - 1;
+  for (int32_t s = 0; s < steps; ++s) {
+    if (T::Mid) {
+      if (s + 1 < steps) wait_stages<T::Loads, T::St - 3>(min(s + T::St - 2, steps - 1) - (s + 1));
+      big_barrier<0>();                        // stage s + 1 has landed, stage s - 1 has been read
+    }
+    if (s + T::St - 1 < steps) load_stage<T>(l, slot, (s + T::St - 1) * T::BK, a.K);
+    if (!T::Mid) {
+      if (s + 1 < steps) wait_stages<T::Loads, T::St - 2>(min(s + T::St - 1, steps - 1) - (s + 1));
+      big_barrier<0>();                        // stage s + 1 has landed, stage s has been read
+    }
+    slot = slot + 1 == T::St ? 0 : slot + 1;
+  }
+}
+
+template <class T>
+__device__ __forceinline__ void multiply(const LinearArgs& a, uint32_t lds0, int lw, int lane, int32_t n0, int32_t m0, int32_t steps) {
+  constexpr int NB = T::NB, MB = T::MB, KK = T::KK, F = NB + MB;
   const int wn = lw >> 1, wm = lw & 1;
   const int col = lane & 31, half = lane >> 5;
 
-  // this lane's bias values, loaded before the loop so that their latency is hidden: columns
-  // n0 + wn*64 + nb*32 + 8 gq + 4 half + e (N is a multiple of 8: a run of 4 is all in or all out)
-  typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
-  u32x2_t bq[2][4];
+  // this lane's bias values, loaded before the loop so that their latency is hidden (N is a
+  // multiple of 8: a run of 4 is all in or all out)
+  u32x2_t bq[NB][4];
 #pragma unroll
-  for (int nb = 0; nb < 2; ++nb)
+  for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
     for (int gq = 0; gq < 4; ++gq) {
-      const int32_t n = n0 + wn * 64 + nb * 32 + 8 * gq + 4 * half;
+      const int32_t n = n0 + wn * 32 * NB + nb * 32 + 8 * gq + 4 * half;
       bq[nb][gq] = (a.bias && n < a.N) ? *reinterpret_cast<const u32x2_t*>(a.bias + n) : u32x2_t{0u, 0u};
     }
 
-  // fragment offsets within a stage: W row wn*64 + nb*32 + col, x row wm*128 + mb*32 + col, chunk
-  // 2 kk + half; rows 32 apart share the swizzle (nb, mb are immediate offsets)
-  uint32_t w_off[4], x_off[4];
+  uint32_t w_off[KK], x_off[KK];
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const int rw = wn * 64 + col, rx = wm * 128 + col;
-    w_off[kk] = lds0 + rw * kRowBytes + (((2 * kk + half) ^ swz(rw)) * 16);
-    x_off[kk] = lds0 + kWBytes + rx * kRowBytes + (((2 * kk + half) ^ swz(rx)) * 16);
+  for (int kk = 0; kk < KK; ++kk) {
+    const int rw = wn * 32 * NB + col, rx = wm * 32 * MB + col;
+    w_off[kk] = lds0 + rw * T::Row + (((2 * kk + half) ^ swz(rw)) * 16);
+    x_off[kk] = lds0 + T::BN * T::Row + rx * T::Row + (((2 * kk + half) ^ swz(rx)) * 16);
   }
+  auto frag = [&](uint32_t cur, int kk, int i) {
+    const uint32_t addr = i < NB ? w_off[kk] + cur + i * 32 * T::Row : x_off[kk] + cur + (i - NB) * 32 * T::Row;
+    return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const lds_u32x4_t*>(uintptr_t(addr)));
+  };
 
-  f32x16_t acc[2][4];
+  f32x16_t acc[NB][MB];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < NB; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x16_t{};
+    for (int j = 0; j < MB; ++j) acc[i][j] = f32x16_t{};
 
-  big_barrier();                               // stage 0 has landed
+  bf16x8_t fr[2][F];
+  big_barrier<0>();                            // stage 0 has landed
+  if (T::Mid)
+#pragma unroll
+    for (int i = 0; i < F; ++i) fr[0][i] = frag(0, 0, i);
+  uint32_t cur = 0;
   for (int32_t s = 0; s < steps; ++s) {
-    const uint32_t cur = uint32_t((s % kBigStages) * kStageBytes);
-    // fragments of a 16-wide k step kk: [0, 1] = W blocks nb, [2..5] = x blocks mb; the reads of
-    // step kk + 1 are issued between the MFMAs of step kk (one after each of the first six), so
-    // only the first step of a stage waits for LDS; the schedule is pinned
-    bf16x8_t fr[2][6];
+    const uint32_t nxt = cur + T::Stage == uint32_t(T::Lds) ? 0u : cur + T::Stage;
+    if (!T::Mid) {
 #pragma unroll
-    for (int i = 0; i < 6; ++i) fr[0][i] = frag(w_off, x_off, cur, 0, i);
-    __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+      for (int i = 0; i < F; ++i) fr[0][i] = frag(cur, 0, i);
+      __builtin_amdgcn_sched_group_barrier(0x100, F, 0);
+    }
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int nb = i >> 2, mb = i & 3;
-        acc[nb][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[kk & 1][nb], fr[kk & 1][2 + mb], acc[nb][mb], 0, 0, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        if (kk < 3 && i < 6) {
-          fr[(kk + 1) & 1][i] = frag(w_off, x_off, cur, kk + 1, i);
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        }
+    for (int kk = 0; kk < KK; ++kk) {
+      // before the last k step: stage s + 1 has landed (its first fragments are read below), and
+      // every fragment of stage s - 1 has been read
+      if (T::Mid && kk == KK - 1) {
+        __builtin_amdgcn_sched_barrier(0);
+        big_barrier<F>();
       }
-    big_barrier();                             // stage s read; stage s + 1 has landed
+#pragma unroll
+      for (int i = 0; i < NB * MB; ++i) {
+        const int nb = i / MB, mb = i % MB;
+        acc[nb][mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[kk & 1][nb], fr[kk & 1][NB + mb], acc[nb][mb], 0, 0, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        constexpr int per = (F + NB * MB - 1) / (NB * MB);
+#pragma unroll
+        for (int r = 0; r < per; ++r)
+          if (i * per + r < F && (T::Mid || kk + 1 < KK)) {
+            fr[(kk + 1) & 1][i * per + r] = kk + 1 < KK ? frag(cur, kk + 1, i * per + r) : frag(nxt, 0, i * per + r);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          }
+      }
+    }
+    cur = nxt;
+    if (!T::Mid) big_barrier<0>();
   }
+  if (T::Mid) big_barrier<0>();                // every wave has read the ring
 
-  // lane holds y[m][n .. n + 3] for tile row wm*128 + mb*32 + col and tile columns
-  // wn*64 + nb*32 + 8 gq + 4 half; rows past M or N hold finite values and are not stored
-  typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
+  // lane holds y[m][n .. n + 3] for tile row wm*32*MB + mb*32 + col and tile columns
+  // wn*32*NB + nb*32 + 8 gq + 4 half; rows past M or N are not stored
 #pragma unroll
-  for (int mb = 0; mb < 4; ++mb) {
-    const int r = wm * 128 + mb * 32 + col;
+  for (int mb = 0; mb < MB; ++mb) {
+    const int r = wm * 32 * MB + mb * 32 + col;
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
+    for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
       for (int gq = 0; gq < 4; ++gq) {
-        const int cn = wn * 64 + nb * 32 + 8 * gq + 4 * half;
+        const int cn = wn * 32 * NB + nb * 32 + 8 * gq + 4 * half;
         bf16x4_t v;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -314,76 +417,77 @@ __device__ __forceinline__ void multiply(const LinearArgs& a, uint32_t lds0, int
           const float bias = __uint_as_float((e & 1) ? (b2 & 0xffff0000u) : (b2 << 16));
           v[e] = (__bf16)(acc[nb][mb][4 * gq + e] + bias);
         }
-        *reinterpret_cast<__attribute__((address_space(3))) bf16x4_t*>(uintptr_t(lds0 + uint32_t(r * kYPitch + cn * 2))) = v;
+        *reinterpret_cast<lds_bf16x4_t*>(uintptr_t(lds0 + uint32_t(r * T::YPitch + cn * 2))) = v;
       }
   }
 }
 
-
-__global__ __launch_bounds__(kPCThreads, 1) void linear_kernel_big(LinearArgs a) {
-  __shared__ __attribute__((aligned(1024))) uint8_t lds[kBigStages * kStageBytes];
-
+template <class T>
+__global__ __launch_bounds__(kPCThreads, 1) void linear_kernel_pc(LinearArgs a) {
+  __shared__ __attribute__((aligned(1024))) uint8_t lds[T::Lds];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool loader = wave >= 4;
-  const int lw = wave & 3;                     // loader index or multiplier index
-
+  // XCD-aware numbering: as in linear_kernel
   const int32_t G = gridDim.x;
   const int32_t xcd = blockIdx.x % kXcds;
   const int32_t g = xcd * (G / kXcds) + min(xcd, G % kXcds) + blockIdx.x / kXcds;
   const int32_t tn = g % a.tiles_n, tm = g / a.tiles_n;
-  const int32_t n0 = tn * kBN, m0 = tm * kBigBM;
+  const int32_t n0 = tn * T::BN, m0 = tm * T::BM;
   const uint32_t lds0 = uint32_t(uintptr_t((__attribute__((address_space(3))) void*)lds));
-  const int32_t steps = a.K / kBK;
-
-  if (loader) {
-#pragma unroll
-    for (int j = 0; j < kLoadsPerWave; ++j) big_load(a, lds0, lw, lane, j, n0, m0, 0);
-    if (steps > 1)
-#pragma unroll
-      for (int j = 0; j < kLoadsPerWave; ++j) big_load(a, lds0 + kStageBytes, lw, lane, j, n0, m0, kBK);
-    wait_loads(steps > 1);                     // stage 0
-    big_barrier();
-    for (int32_t s = 0; s < steps; ++s) {
-      const bool more = s + 2 < steps;
-      if (more) {
-        const uint32_t nxt = lds0 + uint32_t(((s + 2) % kBigStages) * kStageBytes);
-#pragma unroll
-        for (int j = 0; j < kLoadsPerWave; ++j) big_load(a, nxt, lw, lane, j, n0, m0, (s + 2) * kBK);
-      }
-      if (s + 1 < steps) wait_loads(more);     // stage s + 1 (stage s + 2 may still be in flight)
-      big_barrier();
-    }
+  const int32_t steps = (a.K + T::BK - 1) / T::BK;
+  if (wave >= 4) {
+    load_loop<T>(a, lds0, wave - 4, lane, n0, m0, steps);
+    if (T::Mid) big_barrier<0>();
   } else {
-    multiply(a, lds0, lw, lane, n0, m0, steps);
+    multiply<T>(a, lds0, wave, lane, n0, m0, steps);
   }
-  big_barrier();                               // the y tile is in LDS (the ring is free)
+  big_barrier<0>();                            // the y tile is in LDS (the ring is free)
 
-  // all 8 waves store the tile: thread t moves 16-byte piece t % 16 (columns n0 + 8 (t % 16) ..
-  // + 7) of tile rows t / 16 + 32 i, so that a wave writes four whole 256-byte row runs
-  const int c = tid & 15;
+  // all 8 waves store the tile in 16-byte pieces that cover whole row runs
+  constexpr int kPieces = T::BN / 8, kRows = kPCThreads / kPieces;
+  const int c = tid % kPieces;
   const int32_t n = n0 + 8 * c;
 #pragma unroll
-  for (int i = 0; i < kBigBM / 32; ++i) {
-    const int r = (tid >> 4) + 32 * i;
+  for (int i = 0; i < T::BM / kRows; ++i) {
+    const int r = tid / kPieces + kRows * i;
     const int32_t m = m0 + r;
-    const u32x4_t v = *reinterpret_cast<const lds_u32x4_t*>(uintptr_t(lds0 + uint32_t(r * kYPitch + c * 16)));
+    const u32x4_t v = *reinterpret_cast<const lds_u32x4_t*>(uintptr_t(lds0 + uint32_t(r * T::YPitch + c * 16)));
     if (m < a.M && n < a.N) *reinterpret_cast<u32x4_t*>(a.y + int64_t(m) * a.N + n) = v;
   }
+}
+
+template <class T>
+hipError_t launch_pc(LinearArgs a, hipStream_t stream) {
+  a.tiles_m = (a.M + T::BM - 1) / T::BM;
+  a.tiles_n = (a.N + T::BN - 1) / T::BN;
+  hipLaunchKernelGGL(linear_kernel_pc<T>, dim3(unsigned(int64_t(a.tiles_m) * a.tiles_n)), dim3(kPCThreads), 0, stream, a);
+  return hipGetLastError();
+}
+
+// Time of one 64-wide k step over the whole launch (us): every round of work-groups takes at least
+// `step` and the operand bytes of all tiles move at `tbps` together.
+double step_us(int32_t M, int32_t N, int bn, int bm, int slots, double step, double tbps) {
+  const double tiles = double((int64_t(N) + bn - 1) / bn) * double((int64_t(M) + bm - 1) / bm);
+  return std::max(std::ceil(tiles / slots) * step, tiles * (bn + bm) * kRowBytes / (tbps * 1e6));
 }
 
 }  // namespace
 
 hipError_t launch_linear(const uint16_t* x, const uint16_t* w, const uint16_t* bias, uint16_t* y, int32_t M,
                          int32_t N, int32_t K, hipStream_t stream) {
-  // K a multiple of 64 (the model's 1536) with 256-row x tiles addressable by 32-bit offsets:
-  // the direct-to-LDS kernel; anything else: the register-staged one
-  if (K % kBK == 0 && int64_t(kBigBM) * K * 2 < (int64_t(1) << 31)) {
-    LinearArgs a{x, w, bias, y, M, N, K, (M + kBigBM - 1) / kBigBM, (N + kBN - 1) / kBN};
-    const int64_t tiles = int64_t(a.tiles_m) * a.tiles_n;
-    hipLaunchKernelGGL(linear_kernel_big, dim3(unsigned(tiles)), dim3(kPCThreads), 0, stream, a);
-    return hipGetLastError();
+  // tiles whose rows 32-bit offsets address: the direct-to-LDS kernel, with the tile size that the
+  // measured rates above put first (fixed costs of ~3 us are the same for all, so K only scales
+  // the comparison)
+  if (int64_t(256) * K * 2 < (int64_t(1) << 31)) {
+    const LinearArgs a{x, w, bias, y, M, N, K, 0, 0};
+    const double t0 = step_us(M, N, 128, 256, 256, 0.63, 12.3), t1 = step_us(M, N, 128, 128, 256, 0.31, 12.0),
+                 t2 = step_us(M, N, 64, 128, 256, 0.23, 14.5), t3 = step_us(M, N, 64, 64, 256, 0.155, 18.5);
+    const double t = std::min(std::min(t0, t1), std::min(t2, t3));
+    if (t0 == t) return launch_pc<Tile<128, 256, 3, false>>(a, stream);
+    if (t1 == t) return launch_pc<Tile<128, 128, 5, true>>(a, stream);
+    if (t2 == t) return launch_pc<Tile<64, 128, 6, true>>(a, stream);
+    return launch_pc<Tile<64, 64, 5, true>>(a, stream);
   }
   LinearArgs a{x, w, bias, y, M, N, K, (M + kBM - 1) / kBM, (N + kBN - 1) / kBN};
   const int64_t tiles = int64_t(a.tiles_m) * a.tiles_n;
