@@ -1,7 +1,10 @@
 """Python binding of libunstep.so: the windowed-attention chunk step of a causal video
 DiT (UnStep, arXiv 2609.32518) on one AMD MI355X.
 
-Argument marshalling only: every step of the path runs in the library's HIP kernels.
+Argument marshalling only: every step of the path runs in the library's HIP kernels.  The
+per-layer and per-chunk calls first go to the native module ``_calls`` (native/calls.cpp), which
+checks, allocates and enqueues an ordinary call (plain CUDA tensors, the current stream); what it
+does not handle, and every error, goes through the Python code below it.
 PyTorch provides device memory (tensors) and the stream; the library's C ABI
 (include/unstep.h) takes raw pointers.  The binding has the same names as the ABI:
 ``unstep_rope_tables``, ``unstep_kv_append`` (+ ``_qknorm``), ``unstep_window_attn``, ``unstep_step``
@@ -34,6 +37,11 @@ if not os.path.exists(LIB_PATH):
     raise ImportError(f"{LIB_PATH} is missing: build it with `python paper_2609_32518_amd/build.py` "
                       "(there is no non-HIP fallback)")
 lib = ctypes.CDLL(LIB_PATH)
+try:
+    from . import _calls
+except ImportError as e:
+    raise ImportError("the native module _calls is missing or does not load: build it with "
+                      "`python paper_2609_32518_amd/build.py`") from e
 
 _i32, _i64, _f32, _f64 = ctypes.c_int32, ctypes.c_int64, ctypes.c_float, ctypes.c_double
 _vp, _sz = ctypes.c_void_p, ctypes.c_size_t
@@ -202,6 +210,7 @@ class Cache:
                                        ring_frames, self.k.data_ptr(), self.v.data_ptr()))
         self.handle = h
         self._ws: Optional[torch.Tensor] = None
+        self._native = _calls.cache(h.value, self.B, self.H, self.T, self.k)   # None: not a plain CUDA cache
 
     def __del__(self):
         h = getattr(self, "handle", None)
@@ -286,6 +295,10 @@ class Cache:
     def unstep_kv_append(self, start_frame: int, n_frames: int, q: Optional[torch.Tensor], k: torch.Tensor,
                          v: torch.Tensor, cos_t: torch.Tensor, sin_t: torch.Tensor,
                          q_rot: Optional[torch.Tensor] = None, stream=None) -> Optional[torch.Tensor]:
+        if stream is None and self._native is not None:
+            r = _calls.append(self._native, start_frame, n_frames, q, k, v, cos_t, sin_t, q_rot)
+            if r is not None:
+                return r[0]
         ts, hs = self._qkv_strides(q, k, v, n_frames)
         self._tables(cos_t, sin_t, n_frames)
         if q is not None:
@@ -302,6 +315,11 @@ class Cache:
                                 stream=None) -> Optional[torch.Tensor]:
         """unstep_kv_append with the RMS normalisation of q and k over each token's H*128 channels
         (weights: bf16 [H*128])."""
+        if stream is None and self._native is not None:
+            r = _calls.append_qknorm(self._native, start_frame, n_frames, q, k, v, cos_t, sin_t, q_norm_weight,
+                                     k_norm_weight, norm_eps, q_rot)
+            if r is not None:
+                return r[0]
         ts, hs = self._qkv_strides(q, k, v, n_frames)
         self._tables(cos_t, sin_t, n_frames)
         _need(k_norm_weight, "k_norm_weight", (self.H * HEAD_DIM,), torch.bfloat16, self.device)
@@ -318,6 +336,11 @@ class Cache:
                            out: Optional[torch.Tensor] = None, lse: Optional[torch.Tensor] = None,
                            softmax_scale: float = 0.0, workspace: Optional[torch.Tensor] = None,
                            use_split: bool = True, stream=None) -> torch.Tensor:
+        if stream is None and self._native is not None:
+            r = _calls.window_attn(self._native, start_frame, n_frames, window_frames, q_rot, out, lse, softmax_scale,
+                                   workspace, use_split, self)
+            if r is not None:
+                return r
         _need(q_rot, "q_rot", (self.B, n_frames * self.T, self.H, HEAD_DIM), torch.bfloat16, self.device)
         out = self._chunk_out(out, "out", n_frames)
         self._lse(lse, n_frames)
@@ -348,6 +371,11 @@ class Cache:
                     out: Optional[torch.Tensor] = None, lse: Optional[torch.Tensor] = None,
                     softmax_scale: float = 0.0, workspace: Optional[torch.Tensor] = None, use_split: bool = True,
                     stream=None) -> torch.Tensor:
+        if stream is None and self._native is not None:
+            r = _calls.step(self._native, start_frame, n_frames, q, k, v, cos_t, sin_t, window_frames, q_rot, out, lse,
+                            softmax_scale, workspace, use_split, self)
+            if r is not None:
+                return r
         if q is None:
             raise ValueError("unstep_step needs q")
         ts, hs = self._qkv_strides(q, k, v, n_frames)
@@ -399,6 +427,10 @@ def unstep_svd_truncate(w: torch.Tensor, rank: int, bf16: bool = True, stream=No
 def unstep_linear(x: torch.Tensor, w: torch.Tensor, bias: Optional[torch.Tensor] = None,
                   out: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """y = x W^T + b for bf16 x [..., K], W [N, K], b [N]."""
+    if stream is None:
+        r = _calls.linear(x, w, bias, out)
+        if r is not None:
+            return r
     for t in (x, w) + ((bias,) if bias is not None else ()):
         if t.dtype != torch.bfloat16 or not t.is_contiguous():
             raise ValueError("x, w, bias must be contiguous bf16 tensors")
@@ -453,6 +485,10 @@ def _latent(x: torch.Tensor) -> None:
 def unstep_renoise(x: torch.Tensor, eps: torch.Tensor, sigma: float, out: Optional[torch.Tensor] = None,
                    stream=None) -> torch.Tensor:
     """Equation 1: (1 - sigma) x + sigma eps."""
+    if stream is None:
+        r = _calls.flow(False, x, eps, sigma, out)
+        if r is not None:
+            return r
     for t in (x, eps):
         _latent(t)
     if eps.shape != x.shape:
@@ -469,6 +505,10 @@ def unstep_renoise(x: torch.Tensor, eps: torch.Tensor, sigma: float, out: Option
 def unstep_emit(x_tilde: torch.Tensor, v: torch.Tensor, sigma: float, out: Optional[torch.Tensor] = None,
                 stream=None) -> torch.Tensor:
     """Equation 3: x_tilde - sigma v."""
+    if stream is None:
+        r = _calls.flow(True, x_tilde, v, sigma, out)
+        if r is not None:
+            return r
     for t in (x_tilde, v):
         _latent(t)
     if v.shape != x_tilde.shape:
