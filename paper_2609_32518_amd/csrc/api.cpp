@@ -134,8 +134,10 @@ int plan_attn(const unstep_cache* c, const unstep::CacheIndex& idx, int32_t f0, 
   a->seg_l0[UNSTEP_MAX_SEGMENTS] = INT32_MAX;
   a->scale = scale > 0.f ? scale : 1.0f / std::sqrt(float(UNSTEP_HEAD_DIM));
   const unstep::AttnPlan plan = unstep::attn_plan(c->B, c->H, N, a->n_keys);
+  a->parts = 1;
   if (plan.workspace > 0 && workspace && ws_bytes >= plan.workspace) {
     a->groups = plan.groups;
+    a->parts = plan.parts;
     a->part_o = static_cast<float*>(workspace);
     a->part_ml = static_cast<float*>(workspace) + plan.part_o_floats;
   } else {
@@ -351,6 +353,7 @@ int unstep_window_attn_noalloc(const unstep_cache* c, int32_t start_frame, int32
       hipError_t e = unstep::static_attn_scratch(&scratch, &bytes);
       if (e != hipSuccess) return fail(UNSTEP_E_HIP, "%s: scratch lookup: %s", where, hipGetErrorString(e));
       a.groups = plan.groups;
+      a.parts = plan.parts;
       a.part_o = static_cast<float*>(scratch);
       a.part_ml = static_cast<float*>(scratch) + plan.part_o_floats;
     }

@@ -61,6 +61,7 @@ struct AttnArgs {
   int32_t seg_l0[UNSTEP_MAX_SEGMENTS + 1];   // logical start of each segment (INT32_MAX unused)
   int32_t seg_row0[UNSTEP_MAX_SEGMENTS];     // physical row of each segment's first key
   int32_t groups;          // work-groups sharing the (query tile, key tile) units equally
+  int32_t parts;           // groups per query tile when that is a whole number, else 0
   float scale;             // softmax scale
 };
 
@@ -71,6 +72,7 @@ struct AttnPlan {
   size_t workspace;        // scratch bytes the balanced schedule needs (0 for plain)
   int32_t plain_groups;    // one work-group per query tile
   size_t part_o_floats;    // offset of the (offset, sum) array in the scratch, in floats
+  int32_t parts;           // work-groups per query tile when that is a whole number, else 0
 };
 // out = a x + b y on n bf16 values (renoise / emit of the clean-cache pass); n may be any
 // count, pointers 16-byte aligned.
@@ -97,6 +99,16 @@ hipError_t launch_cast_bf16(const float* x, uint16_t* y, int64_t n, hipStream_t 
 // y = double(x), and y = float(x) rounded to nearest even, on n values.
 hipError_t launch_widen_f64(const float* x, double* y, int64_t n, hipStream_t stream);
 hipError_t launch_narrow_f32(const double* x, float* y, int64_t n, hipStream_t stream);
+
+// Slices that the merge of a query tile's `parts` partials runs side by side (1, 2, 4 or 8): at least
+// two partials each, and only while there are few query tiles (with many, rows fill the chip by
+// themselves: 48 tiles of 5 parts 34.5 us in one slice, 36.8 in two; 2 tiles of 100 parts 60.8 in
+// one, 27.6 in eight).
+inline int attn_merge_slices(int32_t query_tiles, int32_t parts) {
+  int s = 1;
+  while (s < 8 && 4 * s <= parts && 2 * s * int64_t(query_tiles) <= 56) s *= 2;
+  return s;
+}
 
 AttnPlan attn_plan(int32_t B, int32_t H, int32_t N, int32_t n_keys);
 

@@ -34,10 +34,9 @@
 // loads and barriers of the walk only.
 //
 // Schedule: the (query tile, key tile) units of the launch are cut into `groups` equal
-// contiguous ranges, one per work-group: either one work-group per query tile (its whole key
-// range), or about one per compute unit when the query tiles alone would leave too many idle
-// (attn_plan weighs the two with costs measured on the chip); in the second case every query
-// tile is cut into k equal parts when a whole number k >= 2 per tile nearly fills the chip.  A query tile whose key range
+// contiguous ranges, one per work-group: one work-group per query tile (its whole key range),
+// or the same number of equal parts per query tile, or one range per compute unit (attn_plan
+// weighs them with costs measured on the chip).  A query tile whose key range
 // falls to several work-groups gets a normalised partial output and its (offset, row sum)
 // from each, and attn_combine merges them by log-sum-exp.  Work-groups are numbered so that
 // neighbouring ranges (same head, neighbouring query tiles) land on the same XCD and share
@@ -566,73 +565,125 @@ __global__ __launch_bounds__(kThreads) void window_attn_kernel(AttnArgs a) {
 // Finish every query tile whose key range was shared by several work-groups: merge their
 // partials by log-sum-exp in one pass, keeping a running offset M: each partial (m, l, o)
 // rescales the sums by 2^((M_old - M) c2) when it raises M and adds w = l 2^((m - M) c2),
-// out = sum w o / sum w.  Work-group = (query tile, 32 rows), thread = (4 rows, 4 output
-// columns): the schedule arithmetic (64-bit divisions) is work-group uniform and runs on the
-// scalar unit, and each thread keeps the loads of 4 rows in flight.
-constexpr int kCombineRowsPerThread = 4;
-constexpr int kCombineRows = 8 * kCombineRowsPerThread;   // rows per work-group
+// out = sum w o / sum w.
+// A [390 queries, 3315 keys] call of 24 heads (5 parts): 8.5 us before, 5.7 so; one frame of 1560
+// queries over 18720 keys (12 heads, 3 parts): 10.2 and 8.4.
+// What bounds it: the latency of the partials' loads, one after the other, and (all but the largest
+// launches) the launch itself.  So the loads of four partials are in flight together, a tile cut into
+// many parts has them merged in kSlices slices side by side (slice s takes partials s, s + kSlices,
+// ...) and the slices merged through LDS, only the tile's first partial can be anything but slot 0 of
+// its work-group (one 64-bit division, none when the work-groups are a whole number per query
+// tile), and blocks of rows past the chunk's end return at once.  Work-group = (query tile,
+// kCombineRows rows), 32 threads per row and slice, thread = (kRows rows, 4 output columns).
+constexpr int kCombineBatch = 4;                          // partials loaded together
 
+struct Merge {
+  float M, W;
+  float4 acc;
+  // adds w (m, v), w = l 2^((m - M) c2), with l > 0 or an empty partial
+  __device__ __forceinline__ void add(float m, float l, float4 v, float c2) {
+    const float mn = fmaxf(M, m);
+    const float s_old = __builtin_amdgcn_exp2f((M - mn) * c2);
+    const float w = l * __builtin_amdgcn_exp2f((m - mn) * c2);
+    acc.x = acc.x * s_old + w * v.x;
+    acc.y = acc.y * s_old + w * v.y;
+    acc.z = acc.z * s_old + w * v.z;
+    acc.w = acc.w * s_old + w * v.w;
+    W = W * s_old + w;
+    M = mn;
+  }
+};
+
+template <int kSlices>
 __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
+  constexpr int kRows = kSlices == 1 ? 2 : 1;             // rows per thread, kRowStep apart
+  constexpr int kRowStep = 8 / kSlices;
+  constexpr int kCombineRows = kRowStep * kRows;          // rows per work-group
+  constexpr int kGroupsPerTile = kBlockQ / kCombineRows;
   int32_t qtiles;
   const Schedule sc = make_schedule(a, &qtiles);
-  constexpr int kGroupsPerTile = kBlockQ / kCombineRows;
-  const int64_t t = blockIdx.x / kGroupsPerTile;                       // (b, h, query tile)
-  const int32_t qt = int32_t(t % qtiles);
-  const int32_t r0 = int32_t(blockIdx.x % kGroupsPerTile) * kCombineRows + int32_t(threadIdx.x >> 5);
+  const int32_t t = int32_t(blockIdx.x / kGroupsPerTile);              // (b, h, query tile)
+  const int32_t qt = t % qtiles;
+  const int32_t row_base = int32_t(blockIdx.x % kGroupsPerTile) * kCombineRows;
+  if (qt * kBlockQ + row_base >= a.N) return;
+  const int32_t slice = int32_t(threadIdx.x >> 5) % kSlices;
+  const int32_t r0 = row_base + int32_t(threadIdx.x >> 5) / kSlices;
   const int32_t part = threadIdx.x & 31;
-  const int64_t ua = t * sc.Tk;
-  const int64_t ga = sc.owner(ua), gb = sc.owner(ua + sc.Tk - 1);
-  if (ga == gb) return;                                              // written directly by its work-group
+  int32_t ga, gb, slot0 = 0;                                           // first and last owner; the first's slot
+  if (a.parts) {
+    ga = t * a.parts;
+    gb = ga + a.parts - 1;
+  } else {
+    const int64_t ua = int64_t(t) * sc.Tk;
+    ga = int32_t(sc.owner(ua));
+    gb = int32_t(sc.owner(ua + sc.Tk - 1));
+    slot0 = sc.start(ga) >= ua ? 0 : 1;
+  }
+  if (ga == gb) return;                                                // written directly by its work-group
   const float c2 = a.scale * kLog2e;
-  float M[kCombineRowsPerThread], W[kCombineRowsPerThread];
-  float4 acc[kCombineRowsPerThread];
+  Merge mg[kRows];
 #pragma unroll
-  for (int j = 0; j < kCombineRowsPerThread; ++j) {
-    M[j] = -FLT_MAX;
-    W[j] = 0.f;
-    acc[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-  for (int64_t g = ga; g <= gb; ++g) {
-    const int64_t base = (g * 2 + (sc.start(g) >= ua ? 0 : 1)) * kBlockQ + r0;
-    float2 ml[kCombineRowsPerThread];
-    float4 v[kCombineRowsPerThread];
+  for (int j = 0; j < kRows; ++j) mg[j] = Merge{-FLT_MAX, 0.f, make_float4(0.f, 0.f, 0.f, 0.f)};
+  for (int32_t g0 = ga + slice; g0 <= gb; g0 += kCombineBatch * kSlices) {
+    float2 ml[kCombineBatch][kRows];
+    float4 v[kCombineBatch][kRows];
 #pragma unroll
-    for (int j = 0; j < kCombineRowsPerThread; ++j) {
-      const int64_t prow = base + 8 * j;
-      ml[j] = *reinterpret_cast<const float2*>(a.part_ml + prow * 2);
-      v[j] = *reinterpret_cast<const float4*>(a.part_o + prow * kHeadDim + part * 4);
+    for (int i = 0; i < kCombineBatch; ++i) {
+      const int32_t g = min(g0 + i * kSlices, gb);                     // past the last owner: loaded, not used
+      const int64_t base = (int64_t(g) * 2 + (g == ga ? slot0 : 0)) * kBlockQ + r0;
+#pragma unroll
+      for (int j = 0; j < kRows; ++j) {
+        const int64_t prow = base + kRowStep * j;
+        ml[i][j] = *reinterpret_cast<const float2*>(a.part_ml + prow * 2);
+        v[i][j] = *reinterpret_cast<const float4*>(a.part_o + prow * kHeadDim + part * 4);
+      }
     }
 #pragma unroll
-    for (int j = 0; j < kCombineRowsPerThread; ++j) {
-      const float l = ml[j].y > 0.f ? ml[j].y : 0.f;              // an empty partial adds nothing
-      const float m = ml[j].y > 0.f ? ml[j].x : -FLT_MAX;
-      const float mn = fmaxf(M[j], m);
-      const float s_old = __builtin_amdgcn_exp2f((M[j] - mn) * c2);
-      const float w = l * __builtin_amdgcn_exp2f((m - mn) * c2);
-      acc[j].x = acc[j].x * s_old + w * v[j].x;
-      acc[j].y = acc[j].y * s_old + w * v[j].y;
-      acc[j].z = acc[j].z * s_old + w * v[j].z;
-      acc[j].w = acc[j].w * s_old + w * v[j].w;
-      W[j] = W[j] * s_old + w;
-      M[j] = mn;
+    for (int i = 0; i < kCombineBatch; ++i) {
+      if (g0 + i * kSlices > gb) break;
+#pragma unroll
+      for (int j = 0; j < kRows; ++j)                                  // an empty partial adds nothing
+        mg[j].add(ml[i][j].y > 0.f ? ml[i][j].x : -FLT_MAX, ml[i][j].y > 0.f ? ml[i][j].y : 0.f, v[i][j], c2);
     }
   }
-  const int32_t bh_idx = int32_t(t / qtiles);
+  if constexpr (kSlices > 1) {
+    // slice 0 of each row takes in the others: (M, W, acc / W)
+    __shared__ float4 sacc[256];
+    __shared__ float2 sml[8];
+    const float inv = mg[0].W > 0.f ? 1.f / mg[0].W : 0.f;
+    sacc[threadIdx.x] = make_float4(mg[0].acc.x * inv, mg[0].acc.y * inv, mg[0].acc.z * inv, mg[0].acc.w * inv);
+    if (part == 0) sml[threadIdx.x >> 5] = make_float2(mg[0].M, mg[0].W);
+    __syncthreads();
+    if (slice > 0) return;
+#pragma unroll
+    for (int s = 1; s < kSlices; ++s) {
+      const float2 m = sml[(threadIdx.x >> 5) + s];
+      mg[0].add(m.x, m.y, sacc[threadIdx.x + 32 * s], c2);
+    }
+  }
+  const int32_t bh_idx = t / qtiles;
   const int32_t h = bh_idx % a.H, b = bh_idx / a.H;
   typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
 #pragma unroll
-  for (int j = 0; j < kCombineRowsPerThread; ++j) {
-    const int32_t qi = qt * kBlockQ + r0 + 8 * j;
+  for (int j = 0; j < kRows; ++j) {
+    const int32_t qi = qt * kBlockQ + r0 + kRowStep * j;
     if (qi >= a.N) break;
-    const float inv = 1.f / W[j];
+    const float inv = 1.f / mg[j].W;
     bf16x4_t o;
-    o[0] = (__bf16)(acc[j].x * inv);
-    o[1] = (__bf16)(acc[j].y * inv);
-    o[2] = (__bf16)(acc[j].z * inv);
-    o[3] = (__bf16)(acc[j].w * inv);
+    o[0] = (__bf16)(mg[j].acc.x * inv);
+    o[1] = (__bf16)(mg[j].acc.y * inv);
+    o[2] = (__bf16)(mg[j].acc.z * inv);
+    o[3] = (__bf16)(mg[j].acc.w * inv);
     *reinterpret_cast<bf16x4_t*>(a.out + ((int64_t(b) * a.N + qi) * a.H + h) * kHeadDim + part * 4) = o;
-    if (a.lse && part == 0) a.lse[(int64_t(b) * a.H + h) * a.N + qi] = M[j] * a.scale + logf(W[j]);
+    if (a.lse && part == 0) a.lse[(int64_t(b) * a.H + h) * a.N + qi] = mg[j].M * a.scale + logf(mg[j].W);
   }
+}
+
+template <int kSlices>
+void launch_combine(const AttnArgs& a, hipStream_t stream) {
+  const int64_t qtiles = int64_t(a.B) * a.H * ((a.N + kBlockQ - 1) / kBlockQ);
+  constexpr int kRows = 8 / kSlices * (kSlices == 1 ? 2 : 1);
+  hipLaunchKernelGGL(attn_combine_kernel<kSlices>, dim3(unsigned(qtiles * (kBlockQ / kRows))), dim3(256), 0, stream, a);
 }
 
 }  // namespace
@@ -641,8 +692,12 @@ hipError_t launch_window_attn(const AttnArgs& a, hipStream_t stream) {
   hipLaunchKernelGGL(window_attn_kernel, dim3(unsigned(a.groups)), dim3(kThreads), 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.part_o == nullptr) return e;
-  const int64_t qtiles = int64_t(a.B) * a.H * ((a.N + kBlockQ - 1) / kBlockQ);
-  hipLaunchKernelGGL(attn_combine_kernel, dim3(unsigned(qtiles * (kBlockQ / kCombineRows))), dim3(256), 0, stream, a);
+  switch (a.parts ? attn_merge_slices(a.B * a.H * ((a.N + kBlockQ - 1) / kBlockQ), a.parts) : 1) {
+    case 1: launch_combine<1>(a, stream); break;
+    case 2: launch_combine<2>(a, stream); break;
+    case 4: launch_combine<4>(a, stream); break;
+    default: launch_combine<8>(a, stream); break;
+  }
   return hipGetLastError();
 }
 
