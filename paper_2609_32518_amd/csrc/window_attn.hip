@@ -10,6 +10,7 @@
 // barriers, and in each phase one wave of a SIMD issues MFMAs while the other computes
 // the softmax of its previous tile.  Per 64-key tile t, per wave:
 //   M phase: O^T += V^T(t-1) * P^T(t-1) and S^T(t) = K(t) * Q^T   (32 MFMAs)
+//   (the first tile's M phase has the QK product only, and a last one the PV product only)
 //   V phase: P(t) = exp2((S(t) - m) * scale * log2(e)) in bf16, row sums   (VALU), and
 //            this wave's share of the loads of a later stage
 // Both products use v_mfma_f32_32x32x16_bf16 with keys (S^T) or head dimensions (O^T) on
@@ -199,8 +200,7 @@ struct Acc {
 __device__ __forceinline__ constexpr int job_id(int j) { return (j & 1) ? 16 + (j >> 1) : (j >> 1); }
 __device__ __forceinline__ constexpr int job_reads(int j) { return job_id(j) < 16 ? 2 : 1; }
 
-__device__ __forceinline__ bf16x8_t fetch_job(int jj, int slot, const Walk& w) {
-  const int j = job_id(jj);
+__device__ __forceinline__ bf16x8_t fetch_id(int j, int slot, const Walk& w) {
   if (j < 16) {
     const uint32_t rel = slot * kTileBytes + (32 * (j >> 3) + 16 * ((j >> 2) & 1)) * kRowBytes;
     const u32x2_t lo = lds_read_tr(w.voff[0][j & 3] + rel);
@@ -211,8 +211,9 @@ __device__ __forceinline__ bf16x8_t fetch_job(int jj, int slot, const Walk& w) {
   return as_bf16x8(*(const lds_u32x4_t*)(uintptr_t)(w.koff[st] + slot * kTileBytes + 32 * kb * kRowBytes));
 }
 
-__device__ __forceinline__ void run_job(Acc& a, int jj, bf16x8_t f, const bf16x8_t (&qf)[8]) {
-  const int j = job_id(jj);
+__device__ __forceinline__ bf16x8_t fetch_job(int jj, int slot, const Walk& w) { return fetch_id(job_id(jj), slot, w); }
+
+__device__ __forceinline__ void run_id(Acc& a, int j, bf16x8_t f, const bf16x8_t (&qf)[8]) {
   if (j < 16) {
     a.o[j & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, a.p[j >> 3][(j >> 2) & 1], a.o[j & 3], 0, 0, 0);
   } else {
@@ -221,6 +222,8 @@ __device__ __forceinline__ void run_job(Acc& a, int jj, bf16x8_t f, const bf16x8
     a.s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, qf[st], st == 0 ? zero : a.s[kb], 0, 0, 0);
   }
 }
+
+__device__ __forceinline__ void run_job(Acc& a, int jj, bf16x8_t f, const bf16x8_t (&qf)[8]) { run_id(a, job_id(jj), f, qf); }
 
 constexpr int kFetchAhead = 4;               // fragments in flight ahead of the MFMA that uses them
 
@@ -240,9 +243,30 @@ struct MJob {
   }
 };
 
-// Every M phase runs all 32 jobs, so the loop has a single path for the accumulators: in
-// the first tile's phase P is still zero (the PV product adds nothing), and in the phase
-// after the last tile the QK product of the duplicate K tile is not used.
+// One product alone, for the two ends of a walk: kFirst 16 the QK product of the first tile (there is
+// no tile before it), kFirst 0 the PV product after the last.  With the queries read while the first
+// stages are on their way, the two ends take 0.7-1.9% off the calls of few key tiles per
+// work-group (24 heads x 390 queries x 3315 keys: 40.1 -> 39.4 us a step) and 0.1-0.5% off the others.
+template <int J, int kFirst>
+struct HalfJob {
+  static __device__ __forceinline__ void run(Acc& a, bf16x8_t (&f)[16], int slot, const bf16x8_t (&qf)[8], const Walk& w) {
+    if constexpr (J + kFetchAhead < 16) f[J + kFetchAhead] = fetch_id(kFirst + J + kFetchAhead, slot, w);
+    run_id(a, kFirst + J, f[J], qf);
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    if constexpr (J + kFetchAhead < 16) __builtin_amdgcn_sched_group_barrier(0x100, kFirst ? 1 : 2, 0);
+    if constexpr (J + 1 < 16) HalfJob<J + 1, kFirst>::run(a, f, slot, qf, w);
+  }
+};
+template <int kFirst>
+__device__ __forceinline__ void half_phase(Acc& a, int slot, const bf16x8_t (&qf)[8], const Walk& w) {
+  bf16x8_t f[16];
+#pragma unroll
+  for (int j = 0; j < kFetchAhead; ++j) f[j] = fetch_id(kFirst + j, slot, w);
+  __builtin_amdgcn_sched_group_barrier(0x100, kFirst ? kFetchAhead : 2 * kFetchAhead, 0);
+  HalfJob<0, kFirst>::run(a, f, slot, qf, w);
+}
+
+// The phases between run all 32 jobs, so the loop has a single path for the accumulators.
 __device__ __forceinline__ void m_phase(Acc& a, int slot, const bf16x8_t (&qf)[8], const Walk& w) {
   bf16x8_t f[32];
 #pragma unroll
@@ -308,44 +332,37 @@ __device__ __forceinline__ void v_phase(Acc& a, int32_t t, Walk& w, int wave) {
 // for everyone when phase 2t + 2 (group A's M phase of tile t + 1) starts.  The slot
 // refilled with stage t + 3 (group A in phase 2t + 1, group B in 2t + 2) last held stage
 // t - 1, read by group B in global phase 2t - 1.
-template <int kMode, int kSlot, bool kOneRun, bool kIdle>
+template <int kMode, int kSlot, bool kOneRun, bool kIdle, bool kFirst = false>
 __device__ __forceinline__ void step(Acc& a, Walk& w, const bf16x8_t (&qf)[8], int wave, int32_t t) {
-  if (t > w.n) return;
+  if (t >= w.n) return;
   constexpr int kLoadSlot = (kSlot + kAhead) % kStages;
-  if (!kIdle) m_phase(a, kSlot, qf, w);
-  if (t + 1 <= w.n) wait_stages_in_flight(min(kAhead - 2, w.n - t - 1));
+  if (!kIdle) {
+    if (kFirst)
+      half_phase<16>(a, kSlot, qf, w);
+    else
+      m_phase(a, kSlot, qf, w);
+  }
+  wait_stages_in_flight(min(kAhead - 2, w.n - t - 1));
   barrier();
   if (kIdle) {
     // a wave with no query of the tile: only its share of the loads, in the same order
-    if (t < w.n && t + kAhead <= w.n) {
+    if (t + kAhead <= w.n) {
       load_rows<kOneRun>(w.lds_k + kLoadSlot * kTileBytes, w.kbase, w, w.kc, wave,
                          w.k_begin + min(t + kAhead, w.n - 1) * kBlockK);
       load_rows<kOneRun>(w.lds_v + kLoadSlot * kTileBytes, w.vbase, w, w.vc, wave,
                          w.k_begin + (t + kAhead - 1) * kBlockK);
     }
-  } else if (t < w.n) {
+  } else {
     v_phase<kMode, kLoadSlot, kOneRun>(a, t, w, wave);
   }
   barrier();
 }
 
-// One walk over the key range.  kMode 0: exponent offsets from the first tile (pass 0);
-// 1: offsets given in a.m_off; 2: exact row max only (a.mx).  Accumulates O^T and the row
-// sums from zero (modes 0 and 1).
-template <int kMode, bool kOneRun, bool kIdle>
-__device__ __forceinline__ void walk(Acc& a, Walk& w, const bf16x8_t (&qf)[8], int wave, int group) {
-  const f32x16_t zero = {};
-#pragma unroll
-  for (int d = 0; d < 4; ++d) a.o[d] = zero;
-  a.l = 0.f;
-  a.mx = -INFINITY;
-  const bf16x8_t pz = {};
-#pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-    for (int sub = 0; sub < 2; ++sub) a.p[kb][sub] = pz;
-  // everything earlier (Q loads, previous stores) has drained: the in-flight accounting
-  // below counts only this walk's stage loads
+// Before a walk: frees the ring and issues its first stages.  Everything earlier has drained, so that
+// the in-flight accounting counts this walk's stage loads only; a caller may issue other loads
+// after it (the accounting waits for at least as much then).
+template <bool kOneRun>
+__device__ __forceinline__ void walk_begin(Walk& w, int wave) {
   __builtin_amdgcn_s_waitcnt(0);
   barrier();                                   // the ring is free
   if (!kOneRun) {                              // loader cursors at the range's first key
@@ -355,15 +372,31 @@ __device__ __forceinline__ void walk(Acc& a, Walk& w, const bf16x8_t (&qf)[8], i
 #pragma unroll
   for (int t = 0; t < kAhead; ++t)
     if (t <= w.n) load_stage<kOneRun>(t, w, wave, t);
+}
+
+// One walk over the key range, begun by walk_begin.  kMode 0: exponent offsets from the first tile (pass 0);
+// 1: offsets given in a.m_off; 2: exact row max only (a.mx).  Accumulates O^T and the row
+// sums from zero (modes 0 and 1).
+template <int kMode, bool kOneRun, bool kIdle>
+__device__ __forceinline__ void walk(Acc& a, Walk& w, const bf16x8_t (&qf)[8], int wave, int group) {
+  const f32x16_t zero = {};
+#pragma unroll
+  for (int d = 0; d < 4; ++d) a.o[d] = zero;
+  a.l = 0.f;
+  a.mx = -INFINITY;
   wait_stages_in_flight(min(kAhead - 1, w.n));
   barrier();                                   // stage 0 is complete: global phase 0
   if (group == 1) barrier();                   // group B idles in phase 0
-  for (int32_t t0 = 0; t0 <= w.n; t0 += kStages) {
-    step<kMode, 0, kOneRun, kIdle>(a, w, qf, wave, t0);
-    step<kMode, 1, kOneRun, kIdle>(a, w, qf, wave, t0 + 1);
-    step<kMode, 2, kOneRun, kIdle>(a, w, qf, wave, t0 + 2);
-    step<kMode, 3, kOneRun, kIdle>(a, w, qf, wave, t0 + 3);
+  step<kMode, 0, kOneRun, kIdle, true>(a, w, qf, wave, 0);
+  for (int32_t t0 = 1; t0 < w.n; t0 += kStages) {
+    step<kMode, 1, kOneRun, kIdle>(a, w, qf, wave, t0);
+    step<kMode, 2, kOneRun, kIdle>(a, w, qf, wave, t0 + 1);
+    step<kMode, 3, kOneRun, kIdle>(a, w, qf, wave, t0 + 2);
+    step<kMode, 0, kOneRun, kIdle>(a, w, qf, wave, t0 + 3);
   }
+  if (!kIdle) half_phase<0>(a, w.n % kStages, qf, w);
+  barrier();
+  barrier();
   if (group == 0) barrier();                   // group A idles in the last phase
 }
 
@@ -457,6 +490,14 @@ __global__ __launch_bounds__(kThreads) void window_attn_kernel(AttnArgs a) {
     w.k_end = min(a.n_keys, k1 * kBlockK);
     w.n = (w.k_end - w.k_begin + kBlockK - 1) / kBlockK;
 
+    // the first stages are on their way before the queries are read: both take a first touch of
+    // memory (about 2 us), which a launch of few tiles would otherwise pay twice
+    const bool one_run = w.k_end <= w.seg.l1;
+    if (one_run)
+      walk_begin<true>(w, wave);
+    else
+      walk_begin<false>(w, wave);
+
     // Q^T fragments: for d-step s, q[query][16 s + 8 half .. +8]
     const int32_t r = wave * 32 + col;                 // row within the query tile
     const int32_t qi = qt * kBlockQ + r;
@@ -478,17 +519,20 @@ __global__ __launch_bounds__(kThreads) void window_attn_kernel(AttnArgs a) {
     // a wave whose 32 queries all lie past the chunk's end (the last, ragged query tile) runs
     // the walk's loads and barriers only
     const bool idle = qt * kBlockQ + wave * 32 >= N;
-    if (w.k_end <= w.seg.l1) {
+    if (one_run) {
       if (idle)
         walk<0, true, true>(acc, w, qf, wave, group);
       else
         walk<0, true, false>(acc, w, qf, wave, group);
       if (__syncthreads_or(!(acc.l <= 0x1p64f))) {
+        walk_begin<true>(w, wave);
         if (idle) {
           walk<2, true, true>(acc, w, qf, wave, group);
+          walk_begin<true>(w, wave);
           walk<1, true, true>(acc, w, qf, wave, group);
         } else {
           walk<2, true, false>(acc, w, qf, wave, group);
+          walk_begin<true>(w, wave);
           acc.m_off = fmaxf(acc.mx, __shfl_xor(acc.mx, 32));
           walk<1, true, false>(acc, w, qf, wave, group);
         }
@@ -499,11 +543,14 @@ __global__ __launch_bounds__(kThreads) void window_attn_kernel(AttnArgs a) {
       else
         walk<0, false, false>(acc, w, qf, wave, group);
       if (__syncthreads_or(!(acc.l <= 0x1p64f))) {
+        walk_begin<false>(w, wave);
         if (idle) {
           walk<2, false, true>(acc, w, qf, wave, group);
+          walk_begin<false>(w, wave);
           walk<1, false, true>(acc, w, qf, wave, group);
         } else {
           walk<2, false, false>(acc, w, qf, wave, group);
+          walk_begin<false>(w, wave);
           acc.m_off = fmaxf(acc.mx, __shfl_xor(acc.mx, 32));
           walk<1, false, false>(acc, w, qf, wave, group);
         }
