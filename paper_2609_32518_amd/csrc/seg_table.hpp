@@ -127,4 +127,19 @@ UNSTEP_HD Segment take_segment(const Schedule& sc, int64_t u_begin, int64_t& u_h
   return s;
 }
 
+// The same when the work-groups are `parts` per query tile: work-group g walks the one segment
+// [i Tk / parts, (i + 1) Tk / parts) of query tile g / parts, i = g % parts (U = tiles Tk and
+// G = tiles parts make start(g) exactly the tile's first unit plus i Tk / parts).  32-bit divisions
+// only: i is below 2^8 and Tk below 2^17.
+UNSTEP_HD Segment part_segment(int32_t Tk, int32_t parts, int32_t g) {
+  Segment s;
+  const int32_t t = g / parts, i = g - t * parts;
+  s.t = t;
+  s.k0 = i * Tk / parts;
+  s.k1 = (i + 1) * Tk / parts;
+  s.slot = 0;
+  s.full = parts == 1;
+  return s;
+}
+
 }  // namespace unstep

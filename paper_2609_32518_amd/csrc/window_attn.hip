@@ -71,6 +71,7 @@ constexpr int kOutPitch = kRowBytes + 16;
 static_assert(kBlockQ * kOutPitch <= 2 * kStages * kTileBytes, "the output tile must fit the ring");
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kXcds = 8;
+constexpr int64_t kShortTiles = 32;           // key tiles of a work-group's range
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
@@ -144,8 +145,9 @@ struct Walk {
 // and other walks keep a cursor per operand.
 // Written as inline assembly: M0 holds the wave's LDS destination, the lane's 16 bytes land
 // at M0 + 16 l.  The scalar base must come from the scalar unit: an SGPR that a VALU instruction
-// wrote (v_readfirstlane) needs 5 wait states before a vector-memory read of it, which the
-// compiler does not insert ahead of inline assembly.
+// wrote (v_readfirstlane, a spilled value read back from a lane) needs 5 wait states before a
+// vector-memory read of it, which the compiler does not insert ahead of inline assembly: the first
+// load of each pair waits them itself.
 template <bool kOneRun>
 __device__ __forceinline__ void load_rows(uint32_t dst, const uint8_t* base, const Walk& w, RowCursor& cur, int wave,
                                           int32_t kt0) {
@@ -158,7 +160,10 @@ __device__ __forceinline__ void load_rows(uint32_t dst, const uint8_t* base, con
     for (int i = 0; i < 2; ++i) {
       const uint32_t off = w.loff[i];
       const uint32_t m0 = dst + (8 * wave + 4 * i) * kRowBytes;
-      asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(tb), "{m0}"(m0) : "memory");
+      if (i == 0)
+        asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(tb), "{m0}"(m0) : "memory");
+      else
+        asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(tb), "{m0}"(m0) : "memory");
     }
     return;
   }
@@ -168,7 +173,10 @@ __device__ __forceinline__ void load_rows(uint32_t dst, const uint8_t* base, con
   for (int i = 0; i < 2; ++i) {
     const uint32_t off = uint32_t(rows[i]) * kRowBytes + w.lpiece[i];
     const uint32_t m0 = dst + (8 * wave + 4 * i) * kRowBytes;
-    asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(m0) : "memory");
+    if (i == 0)
+      asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(m0) : "memory");
+    else
+      asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(m0) : "memory");
   }
 }
 
@@ -279,7 +287,7 @@ __device__ __forceinline__ void m_phase(Acc& a, int slot, const bf16x8_t (&qf)[8
 // V phase of tile t: mask keys past the range (last tile), the exponent offsets (first
 // tile of pass 0), then P and its row sums (kMode 2: only the row max), with this wave's
 // share of the loads of stage t + 3 issued before and after the arithmetic.
-template <int kMode, int kLoadSlot, bool kOneRun>
+template <int kMode, int kLoadSlot, bool kOneRun, bool kFirst>
 __device__ __forceinline__ void v_phase(Acc& a, int32_t t, Walk& w, int wave) {
   // this wave's share of stage t + 3 (K tile t + 3, V tile t + 2) into the slot that held
   // stage t - 1
@@ -299,7 +307,7 @@ __device__ __forceinline__ void v_phase(Acc& a, int32_t t, Walk& w, int wave) {
     if (load) load_rows<kOneRun>(w.lds_v + kLoadSlot * kTileBytes, w.vbase, w, w.vc, wave, w.k_begin + (t + kAhead - 1) * kBlockK);
     return;
   }
-  if (kMode == 0 && t == 0) {
+  if (kMode == 0 && kFirst) {
     float m = a.s[0][0];
 #pragma unroll
     for (int i = 0; i < 16; ++i) m = fmaxf(fmaxf(m, a.s[0][i]), a.s[1][i]);
@@ -353,7 +361,7 @@ __device__ __forceinline__ void step(Acc& a, Walk& w, const bf16x8_t (&qf)[8], i
                          w.k_begin + (t + kAhead - 1) * kBlockK);
     }
   } else {
-    v_phase<kMode, kLoadSlot, kOneRun>(a, t, w, wave);
+    v_phase<kMode, kLoadSlot, kOneRun, kFirst>(a, t, w, wave);
   }
   barrier();
 }
@@ -410,6 +418,9 @@ __device__ __forceinline__ Schedule make_schedule(const AttnArgs& a, int32_t* qt
   return sc;
 }
 
+// kParts: a whole number of work-groups per query tile (a.parts), so one segment each, found
+// without the 64-bit divisions of the general split.
+template <bool kParts>
 __global__ __launch_bounds__(kThreads) void window_attn_kernel(AttnArgs a) {
   // K ring (kStages tiles), then V ring: fragment reads address a slot by an immediate
   // offset from a per-lane base register (all offsets within a ring stay below 64 KB)
@@ -471,16 +482,17 @@ __global__ __launch_bounds__(kThreads) void window_attn_kernel(AttnArgs a) {
   // Segments (query tile, key-tile range) of this work-group's unit range, walked from
   // the last to the first: every work-group then starts at the first key tile of a query
   // tile, so work-groups stream the same keys at about the same time (shared L2).
-  const int64_t u_begin = sc.start(g);
-  for (int64_t u_hi = sc.start(int64_t(g) + 1); u_hi > u_begin;) {
-    const Segment sg = take_segment(sc, u_begin, u_hi);
-    const int64_t t = sg.t;
+  const int64_t u_begin = kParts ? 0 : sc.start(g);
+  int64_t u_hi = kParts ? 0 : sc.start(int64_t(g) + 1);
+  do {
+    const Segment sg = kParts ? part_segment(sc.Tk, a.parts, g) : take_segment(sc, u_begin, u_hi);
+    const int32_t t = int32_t(sg.t);                 // fewer than 2^23 query tiles
     const int32_t k0 = sg.k0, k1 = sg.k1;
     const int slot = sg.slot;
     const bool full = sg.full;
 
-    const int32_t qt = int32_t(t % qtiles);
-    const int32_t bh_idx = int32_t(t / qtiles);      // b * H + h
+    const int32_t qt = t % qtiles;
+    const int32_t bh_idx = t / qtiles;               // b * H + h
     const int32_t h = bh_idx % H;
     const int32_t b = bh_idx / H;
     const int64_t bh = int64_t(bh_idx) * a.slots * kHeadDim;
@@ -606,7 +618,7 @@ __global__ __launch_bounds__(kThreads) void window_attn_kernel(AttnArgs a) {
         a.part_ml[prow * 2 + 1] = l_tot;
       }
     }
-  }
+  } while (!kParts && u_hi > u_begin);
 }
 
 // Finish every query tile whose key range was shared by several work-groups: merge their
@@ -736,7 +748,14 @@ void launch_combine(const AttnArgs& a, hipStream_t stream) {
 }  // namespace
 
 hipError_t launch_window_attn(const AttnArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL(window_attn_kernel, dim3(unsigned(a.groups)), dim3(kThreads), 0, stream, a);
+  // Short ranges take the one-segment kernel: it starts ~0.9 us sooner, but its walk, compiled to
+  // other registers, runs 1.3% slower per key tile (24 heads x 390 queries x 3315 keys, 11 tiles:
+  // 38.8 -> 37.8 us a step; 293 tiles: 467 -> 474).
+  const int64_t tk = (a.n_keys + kBlockK - 1) / kBlockK;
+  if (a.parts && (tk + a.parts - 1) / a.parts <= kShortTiles)
+    hipLaunchKernelGGL(window_attn_kernel<true>, dim3(unsigned(a.groups)), dim3(kThreads), 0, stream, a);
+  else
+    hipLaunchKernelGGL(window_attn_kernel<false>, dim3(unsigned(a.groups)), dim3(kThreads), 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.part_o == nullptr) return e;
   switch (a.parts ? attn_merge_slices(a.B * a.H * ((a.N + kBlockQ - 1) / kBlockQ), a.parts) : 1) {
