@@ -207,17 +207,17 @@ class Plan:
 
     def attn_launch_shape(self, f0, C, W):
         """(work-groups, MFMAs per multiplying wave) of the attention launch of a call: one
-        work-group per 256-query tile walking all its key tiles (one M phase more than tiles),
-        or the balanced split's work-groups (from the workspace the call needs), each walking
+        work-group per 256-query tile walking all its key tiles (32 MFMAs each),
+        or the split's work-groups (from the workspace the call needs), each walking
         about its share of the (query tile, key tile) units in up to two segments."""
         wl = self.wl
         qtiles = wl.B * wl.H * -(-C * wl.T // 256)
         tk = -(-self.keys(f0, C, W) // 64)
         need = 0 if self.no_split else self.sets[0]["cache"].workspace_bytes(f0, C, W)
         if need == 0:
-            return qtiles, 32 * (tk + 1)
+            return qtiles, 32 * tk
         groups = need // (2 * 256 * 130 * 4)
-        return groups, 32 * (-(-qtiles * tk // groups) + 2)
+        return groups, 32 * -(-qtiles * tk // groups)
 
     def _prefill(self, cache, randn, seed):
         wl = self.wl
@@ -468,8 +468,8 @@ def summarize_profile(d, workload="full_chunk", qknorm=False):
 
     def kname(n):
         m = re.search(r"::(\w+_kernel)(<[^>]*>)?\(", n)
-        if m:
-            return m.group(1) + (m.group(2) or "")
+        if m:        # the attention's and the merge's instantiations count as one kernel each
+            return m.group(1) + ("" if m.group(1) in ("window_attn_kernel", "attn_combine_kernel") else m.group(2) or "")
         return "copy" if "copyBuffer" in n or "copy" in n.lower() else n[:40]
 
     def counters(name):
@@ -896,11 +896,11 @@ def mfma_reference_us(u, torch, groups, waves_per_simd, mfmas, launches):
 
 def mfma_reference_bench(u, torch, args):
     """The MFMA rate reference in the launch shapes of the full-frame chunk's attention (228
-    work-groups, two multiplying waves per SIMD, 32 MFMAs per key tile plus one M phase: 9408
+    work-groups, two multiplying waves per SIMD, 32 MFMAs per key tile: 9376
     per wave) and of its output projection (228 work-groups, one multiplying wave per SIMD, 768
     MFMAs per wave)."""
     steps = max(args.steps, 30)
-    shapes = {"attention_full_chunk": (228, 2, 32 * (293 + 1)), "projection_4680x1536x1536": (228, 1, 768)}
+    shapes = {"attention_full_chunk": (228, 2, 32 * 293), "projection_4680x1536x1536": (228, 1, 768)}
     res = {"metric": "MFMA-only µs per launch on random bf16 operands", "unit": "us", "higher_is_better": False,
            "launches": steps, "shapes": {}}
     for name, (groups, wps, mfmas) in shapes.items():
