@@ -146,8 +146,8 @@ struct Walk {
 // Written as inline assembly: M0 holds the wave's LDS destination, the lane's 16 bytes land
 // at M0 + 16 l.  The scalar base must come from the scalar unit: an SGPR that a VALU instruction
 // wrote (v_readfirstlane, a spilled value read back from a lane) needs 5 wait states before a
-// vector-memory read of it, which the compiler does not insert ahead of inline assembly: the first
-// load of each pair waits them itself.
+// vector-memory read of it, and a scalar write of M0 one before a load that uses it, which the
+// compiler does not insert ahead of inline assembly: the loads wait them themselves.
 template <bool kOneRun>
 __device__ __forceinline__ void load_rows(uint32_t dst, const uint8_t* base, const Walk& w, RowCursor& cur, int wave,
                                           int32_t kt0) {
@@ -163,7 +163,7 @@ __device__ __forceinline__ void load_rows(uint32_t dst, const uint8_t* base, con
       if (i == 0)
         asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(tb), "{m0}"(m0) : "memory");
       else
-        asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(tb), "{m0}"(m0) : "memory");
+        asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(tb), "{m0}"(m0) : "memory");
     }
     return;
   }
@@ -176,7 +176,7 @@ __device__ __forceinline__ void load_rows(uint32_t dst, const uint8_t* base, con
     if (i == 0)
       asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(m0) : "memory");
     else
-      asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(m0) : "memory");
+      asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(m0) : "memory");
   }
 }
 
