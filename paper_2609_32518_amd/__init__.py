@@ -3,8 +3,8 @@ DiT (UnStep, arXiv 2609.32518) on one AMD MI355X.
 
 Argument marshalling only: every step of the path runs in the library's HIP kernels.  The
 per-layer and per-chunk calls first go to the native module ``_calls`` (native/calls.cpp), which
-checks, allocates and enqueues an ordinary call (plain CUDA tensors, the current stream); what it
-does not handle, and every error, goes through the Python code below it.
+checks, allocates and enqueues an ordinary call (plain CUDA tensors, the current stream) and raises the
+library's error if that call fails; what it does not take goes through the Python code below it.
 PyTorch provides device memory (tensors) and the stream; the library's C ABI
 (include/unstep.h) takes raw pointers.  The binding has the same names as the ABI:
 ``unstep_rope_tables``, ``unstep_kv_append`` (+ ``_qknorm``), ``unstep_window_attn``, ``unstep_step``

@@ -6,9 +6,11 @@
 // (a projection 10.9, a renoise + emit pair 18.4); from here the same calls take a fraction of that.
 //
 // Each function handles the ordinary call (plain strided CUDA tensors of the shapes, types and
-// strides the kernels assume, the current stream) and returns its result; for anything else,
-// an error of the library included, it returns None, and the caller's
-// Python path, which checks everything again, handles the call or raises.
+// strides the kernels assume, the current stream) and returns its result.  For anything else it
+// returns None before the library's call, and the caller's Python path, which checks everything again,
+// handles the call or raises.  Once the library's call has been made nothing goes back to that path:
+// kernels of a call that reports an error may be on the stream already, and run again an update in
+// place would be applied twice.
 #include <Python.h>
 
 #include <ATen/ATen.h>
@@ -75,13 +77,35 @@ PyObject* none() {
   Py_RETURN_NONE;
 }
 
-// Runs the library call without the GIL; true if it succeeded.
+// A Python reference owned here.
+struct Ref {
+  PyObject* o;
+  explicit Ref(PyObject* x) : o(x) {}
+  Ref(const Ref&) = delete;
+  ~Ref() { Py_XDECREF(o); }
+  PyObject* release() {
+    PyObject* r = o;
+    o = nullptr;
+    return r;
+  }
+};
+
+// Sets the package's UnstepError(rc, message) for the library's last error on this thread.
+void raise(int rc) {
+  const Ref pkg{PyImport_ImportModule("paper_2609_32518_amd")};
+  const Ref type{pkg.o ? PyObject_GetAttrString(pkg.o, "UnstepError") : nullptr};
+  const Ref err{type.o ? PyObject_CallFunction(type.o, "is", rc, unstep_last_error()) : nullptr};
+  if (err.o) PyErr_SetObject(type.o, err.o);
+}
+
+// Runs the library call without the GIL; on an error of the library false, with that error raised.
 template <class F>
 bool call(F&& f) {
   int rc;
   Py_BEGIN_ALLOW_THREADS;
   rc = f();
   Py_END_ALLOW_THREADS;
+  if (rc != UNSTEP_OK) raise(rc);
   return rc == UNSTEP_OK;
 }
 
@@ -146,12 +170,21 @@ const at::Tensor* chunk_out(const CacheInfo& c, int64_t N, PyObject* o, at::Tens
   return is(t, at::kBFloat16, at::IntArrayRef(shape, 4), c.device) ? t : nullptr;
 }
 
-PyObject* result(PyObject* given, const at::Tensor& made) {
+// The object that a call returns, made before the library's call (null, with a Python error, if that
+// fails).
+Ref result(PyObject* given, const at::Tensor& made) {
   if (given != Py_None) {
     Py_INCREF(given);
-    return given;
+    return Ref{given};
   }
-  return THPVariable_Wrap(made);
+  return Ref{THPVariable_Wrap(made)};
+}
+
+// What the appends return: a tuple of the rotated queries, or of None without queries.
+Ref append_result(bool with_q, PyObject* given, const at::Tensor& made) {
+  if (!with_q) return Ref{Py_BuildValue("(O)", Py_None)};
+  Ref r = result(given, made);
+  return Ref{r.o ? Py_BuildValue("(N)", r.release()) : nullptr};
 }
 
 // lse: None or fp32 [B, H, N]
@@ -164,12 +197,6 @@ bool lse_of(const CacheInfo& c, int64_t N, PyObject* o, float** p) {
   *p = t->data_ptr<float>();
   return true;
 }
-
-// A Python reference owned here.
-struct Ref {
-  PyObject* o;
-  ~Ref() { Py_XDECREF(o); }
-};
 
 // The split-key scratch: the given tensor, or (use_split) the one the Cache object keeps as _ws,
 // replaced by a larger one when it is too small, as Cache.workspace does.  The kept tensor is held in
@@ -235,14 +262,15 @@ PyObject* f_append(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const at::Tensor* qr = nullptr;
     if (k.q && !(qr = chunk_out(*c, k.N, a[8], &made))) return none();
     if (!k.q && a[8] != Py_None) return none();
+    Ref r = append_result(k.q != nullptr, a[8], made);
+    if (!r.o) return none();
     void* st = current_stream();
     if (!call([&] {
           return unstep_kv_append(c->handle, k.f0, k.C, k.q ? k.q->data_ptr() : nullptr, k.k->data_ptr(), k.v->data_ptr(), k.ts, k.hs,
                                   k.cos->data_ptr<float>(), k.sin->data_ptr<float>(), qr ? qr->data_ptr() : nullptr, st);
         }))
-      return none();
-    PyObject* r = k.q ? result(a[8], made) : (Py_INCREF(Py_None), Py_None);
-    return r ? Py_BuildValue("(N)", r) : nullptr;
+      return nullptr;
+    return r.release();
   });
 }
 
@@ -263,15 +291,16 @@ PyObject* f_append_qknorm(PyObject*, PyObject* const* a, Py_ssize_t n) {
     } else if (a[8] != Py_None || a[11] != Py_None) {
       return none();
     }
+    Ref r = append_result(k.q != nullptr, a[11], made);
+    if (!r.o) return none();
     void* st = current_stream();
     if (!call([&] {
           return unstep_kv_append_qknorm(c->handle, k.f0, k.C, k.q ? k.q->data_ptr() : nullptr, k.k->data_ptr(), k.v->data_ptr(), k.ts,
                                          k.hs, k.cos->data_ptr<float>(), k.sin->data_ptr<float>(), wq ? wq->data_ptr() : nullptr,
                                          wk->data_ptr(), eps, qr ? qr->data_ptr() : nullptr, st);
         }))
-      return none();
-    PyObject* r = k.q ? result(a[11], made) : (Py_INCREF(Py_None), Py_None);
-    return r ? Py_BuildValue("(N)", r) : nullptr;
+      return nullptr;
+    return r.release();
   });
 }
 
@@ -294,12 +323,14 @@ PyObject* f_window_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
       return none();
     const at::Tensor* out = chunk_out(*c, N, a[5], &made);
     if (!out) return none();
+    Ref r = result(a[5], made);
+    if (!r.o) return none();
     void* st = current_stream();
     if (!call([&] {
           return unstep_window_attn(c->handle, f0, C, W, q->data_ptr(), out->data_ptr(), lse, float(scale), ws, bytes, st);
         }))
-      return none();
-    return result(a[5], made);
+      return nullptr;
+    return r.release();
   });
 }
 
@@ -320,14 +351,16 @@ PyObject* f_step(PyObject*, PyObject* const* a, Py_ssize_t n) {
     at::Tensor made_q, made;
     const at::Tensor *qr = chunk_out(*c, k.N, a[9], &made_q), *out = qr ? chunk_out(*c, k.N, a[10], &made) : nullptr;
     if (!out) return none();
+    Ref r = result(a[10], made);
+    if (!r.o) return none();
     void* st = current_stream();
     if (!call([&] {
           return unstep_step(c->handle, k.f0, k.C, W, k.q->data_ptr(), k.k->data_ptr(), k.v->data_ptr(), k.ts, k.hs,
                              k.cos->data_ptr<float>(), k.sin->data_ptr<float>(), qr->data_ptr(), out->data_ptr(), lse, float(scale), ws,
                              bytes, st);
         }))
-      return none();
-    return result(a[10], made);
+      return nullptr;
+    return r.release();
   });
 }
 
@@ -354,13 +387,15 @@ PyObject* f_linear(PyObject*, PyObject* const* a, Py_ssize_t n) {
     } else if (!is(out = plain(a[3]), at::kBFloat16, shape, x->device())) {
       return none();
     }
+    Ref r = result(a[3], made);
+    if (!r.o) return none();
     void* st = current_stream();
     if (!call([&] {
           return unstep_linear(x->data_ptr(), w->data_ptr(), b ? b->data_ptr() : nullptr, out->data_ptr(), int32_t(M), int32_t(N),
                                int32_t(K), st);
         }))
-      return none();
-    return result(a[3], made);
+      return nullptr;
+    return r.release();
   });
 }
 
@@ -383,13 +418,15 @@ PyObject* f_flow(PyObject*, PyObject* const* a, Py_ssize_t n) {
       return none();
     }
     const bool emit = a[0] == Py_True;
+    Ref r = result(a[4], made);
+    if (!r.o) return none();
     void* st = current_stream();
     if (!call([&] {
           return emit ? unstep_emit(x->data_ptr(), y->data_ptr(), sigma, out->data_ptr(), x->numel(), st)
                       : unstep_renoise(x->data_ptr(), y->data_ptr(), sigma, out->data_ptr(), x->numel(), st);
         }))
-      return none();
-    return result(a[4], made);
+      return nullptr;
+    return r.release();
   });
 }
 
