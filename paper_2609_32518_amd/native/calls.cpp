@@ -99,6 +99,8 @@ void raise(int rc) {
 }
 
 // Runs the library call without the GIL; on an error of the library false, with that error raised.
+// A tensor's data_ptr may throw (a storage without memory), so the pointers are read before this: an
+// exception must not leave a region without the GIL.
 template <class F>
 bool call(F&& f) {
   int rc;
@@ -130,7 +132,11 @@ struct Chunk {
   int64_t N;
   const at::Tensor *q, *k, *v, *cos, *sin;
   int64_t ts, hs;
+  const void *qp, *kp, *vp;
+  const float *cp, *sp;
 };
+
+void* ptr(const at::Tensor* t) { return t ? t->data_ptr() : nullptr; }
 
 bool chunk_of(const CacheInfo& c, PyObject* const* a, bool q_optional, Chunk* o) {
   if (!to_i32(a[0], &o->f0) || !to_i32(a[1], &o->C) || o->C < 1) return false;
@@ -156,7 +162,14 @@ bool chunk_of(const CacheInfo& c, PyObject* const* a, bool q_optional, Chunk* o)
   const int64_t tab[2] = {o->N, kD / 2};
   o->cos = plain(a[5]);
   o->sin = plain(a[6]);
-  return is(o->cos, at::kFloat, at::IntArrayRef(tab, 2), c.device) && is(o->sin, at::kFloat, at::IntArrayRef(tab, 2), c.device);
+  if (!is(o->cos, at::kFloat, at::IntArrayRef(tab, 2), c.device) || !is(o->sin, at::kFloat, at::IntArrayRef(tab, 2), c.device))
+    return false;
+  o->qp = ptr(o->q);
+  o->kp = ptr(o->k);
+  o->vp = ptr(o->v);
+  o->cp = static_cast<const float*>(ptr(o->cos));
+  o->sp = static_cast<const float*>(ptr(o->sin));
+  return true;
 }
 
 // A given [B, N, H, 128] output checked, or a new one in *made.
@@ -194,7 +207,7 @@ bool lse_of(const CacheInfo& c, int64_t N, PyObject* o, float** p) {
   const int64_t shape[3] = {c.B, c.H, N};
   const at::Tensor* t = plain(o);
   if (!is(t, at::kFloat, at::IntArrayRef(shape, 3), c.device)) return false;
-  *p = t->data_ptr<float>();
+  *p = static_cast<float*>(ptr(t));
   return true;
 }
 
@@ -264,11 +277,8 @@ PyObject* f_append(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (!k.q && a[8] != Py_None) return none();
     Ref r = append_result(k.q != nullptr, a[8], made);
     if (!r.o) return none();
-    void* st = current_stream();
-    if (!call([&] {
-          return unstep_kv_append(c->handle, k.f0, k.C, k.q ? k.q->data_ptr() : nullptr, k.k->data_ptr(), k.v->data_ptr(), k.ts, k.hs,
-                                  k.cos->data_ptr<float>(), k.sin->data_ptr<float>(), qr ? qr->data_ptr() : nullptr, st);
-        }))
+    void *st = current_stream(), *qrp = ptr(qr);
+    if (!call([&] { return unstep_kv_append(c->handle, k.f0, k.C, k.qp, k.kp, k.vp, k.ts, k.hs, k.cp, k.sp, qrp, st); }))
       return nullptr;
     return r.release();
   });
@@ -293,11 +303,9 @@ PyObject* f_append_qknorm(PyObject*, PyObject* const* a, Py_ssize_t n) {
     }
     Ref r = append_result(k.q != nullptr, a[11], made);
     if (!r.o) return none();
-    void* st = current_stream();
+    void *st = current_stream(), *qrp = ptr(qr), *wqp = ptr(wq), *wkp = ptr(wk);
     if (!call([&] {
-          return unstep_kv_append_qknorm(c->handle, k.f0, k.C, k.q ? k.q->data_ptr() : nullptr, k.k->data_ptr(), k.v->data_ptr(), k.ts,
-                                         k.hs, k.cos->data_ptr<float>(), k.sin->data_ptr<float>(), wq ? wq->data_ptr() : nullptr,
-                                         wk->data_ptr(), eps, qr ? qr->data_ptr() : nullptr, st);
+          return unstep_kv_append_qknorm(c->handle, k.f0, k.C, k.qp, k.kp, k.vp, k.ts, k.hs, k.cp, k.sp, wqp, wkp, eps, qrp, st);
         }))
       return nullptr;
     return r.release();
@@ -325,10 +333,8 @@ PyObject* f_window_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (!out) return none();
     Ref r = result(a[5], made);
     if (!r.o) return none();
-    void* st = current_stream();
-    if (!call([&] {
-          return unstep_window_attn(c->handle, f0, C, W, q->data_ptr(), out->data_ptr(), lse, float(scale), ws, bytes, st);
-        }))
+    void *st = current_stream(), *qp = ptr(q), *op = ptr(out);
+    if (!call([&] { return unstep_window_attn(c->handle, f0, C, W, qp, op, lse, float(scale), ws, bytes, st); }))
       return nullptr;
     return r.release();
   });
@@ -353,11 +359,10 @@ PyObject* f_step(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (!out) return none();
     Ref r = result(a[10], made);
     if (!r.o) return none();
-    void* st = current_stream();
+    void *st = current_stream(), *qrp = ptr(qr), *op = ptr(out);
     if (!call([&] {
-          return unstep_step(c->handle, k.f0, k.C, W, k.q->data_ptr(), k.k->data_ptr(), k.v->data_ptr(), k.ts, k.hs,
-                             k.cos->data_ptr<float>(), k.sin->data_ptr<float>(), qr->data_ptr(), out->data_ptr(), lse, float(scale), ws,
-                             bytes, st);
+          return unstep_step(c->handle, k.f0, k.C, W, k.qp, k.kp, k.vp, k.ts, k.hs, k.cp, k.sp, qrp, op, lse, float(scale), ws, bytes,
+                             st);
         }))
       return nullptr;
     return r.release();
@@ -389,11 +394,8 @@ PyObject* f_linear(PyObject*, PyObject* const* a, Py_ssize_t n) {
     }
     Ref r = result(a[3], made);
     if (!r.o) return none();
-    void* st = current_stream();
-    if (!call([&] {
-          return unstep_linear(x->data_ptr(), w->data_ptr(), b ? b->data_ptr() : nullptr, out->data_ptr(), int32_t(M), int32_t(N),
-                               int32_t(K), st);
-        }))
+    void *st = current_stream(), *xp = ptr(x), *wp = ptr(w), *bp = ptr(b), *op = ptr(out);
+    if (!call([&] { return unstep_linear(xp, wp, bp, op, int32_t(M), int32_t(N), int32_t(K), st); }))
       return nullptr;
     return r.release();
   });
@@ -418,13 +420,11 @@ PyObject* f_flow(PyObject*, PyObject* const* a, Py_ssize_t n) {
       return none();
     }
     const bool emit = a[0] == Py_True;
+    const int64_t count = x->numel();
     Ref r = result(a[4], made);
     if (!r.o) return none();
-    void* st = current_stream();
-    if (!call([&] {
-          return emit ? unstep_emit(x->data_ptr(), y->data_ptr(), sigma, out->data_ptr(), x->numel(), st)
-                      : unstep_renoise(x->data_ptr(), y->data_ptr(), sigma, out->data_ptr(), x->numel(), st);
-        }))
+    void *st = current_stream(), *xp = ptr(x), *yp = ptr(y), *op = ptr(out);
+    if (!call([&] { return emit ? unstep_emit(xp, yp, sigma, op, count, st) : unstep_renoise(xp, yp, sigma, op, count, st); }))
       return nullptr;
     return r.release();
   });

@@ -8,35 +8,37 @@ extern "C" {
 int stub_calls = 0;         // calls of any entry point that would enqueue work
 int stub_fail_next = 0;     // status of the next such call; UNSTEP_OK for the others
 const void* stub_handle = nullptr;   // the handle of the last one
+const void* stub_pointer = nullptr;  // its cos or sin table if one of them is null, or its log-sum-exp
 size_t stub_workspace = 0;  // what unstep_attn_workspace_size reports
 
-static int called(const void* handle = nullptr) {
+static int called(const void* handle = nullptr, const void* p = nullptr, const void* p2 = nullptr) {
   ++stub_calls;
   stub_handle = handle;
+  stub_pointer = p && p2 ? p : nullptr;
   const int rc = stub_fail_next;
   stub_fail_next = UNSTEP_OK;
   return rc;
 }
 
 const char* unstep_last_error(void) { return "the stub's error"; }
-int unstep_kv_append(unstep_cache* c, int32_t, int32_t, const void*, const void*, const void*, int64_t, int64_t, const float*,
-                     const float*, void*, void*) {
-  return called(c);
+int unstep_kv_append(unstep_cache* c, int32_t, int32_t, const void*, const void*, const void*, int64_t, int64_t, const float* cos,
+                     const float* sin, void*, void*) {
+  return called(c, cos, sin);
 }
 int unstep_kv_append_qknorm(unstep_cache* c, int32_t, int32_t, const void*, const void*, const void*, int64_t, int64_t,
-                            const float*, const float*, const void*, const void*, double, void*, void*) {
-  return called(c);
+                            const float* cos, const float* sin, const void*, const void*, double, void*, void*) {
+  return called(c, cos, sin);
 }
 int unstep_attn_workspace_size(const unstep_cache*, int32_t, int32_t, int32_t, size_t* bytes) {
   *bytes = stub_workspace;
   return UNSTEP_OK;
 }
-int unstep_window_attn(const unstep_cache* c, int32_t, int32_t, int32_t, const void*, void*, float*, float, void*, size_t, void*) {
-  return called(c);
+int unstep_window_attn(const unstep_cache* c, int32_t, int32_t, int32_t, const void*, void*, float* lse, float, void*, size_t, void*) {
+  return called(c, lse, lse);
 }
-int unstep_step(unstep_cache* c, int32_t, int32_t, int32_t, const void*, const void*, const void*, int64_t, int64_t, const float*,
-                const float*, void*, void*, float*, float, void*, size_t, void*) {
-  return called(c);
+int unstep_step(unstep_cache* c, int32_t, int32_t, int32_t, const void*, const void*, const void*, int64_t, int64_t, const float* cos,
+                const float* sin, void*, void*, float*, float, void*, size_t, void*) {
+  return called(c, cos, sin);
 }
 int unstep_linear(const void*, const void*, const void*, void*, int32_t, int32_t, int32_t, void*) { return called(); }
 int unstep_renoise(const void*, const void*, double, void*, int64_t, void*) { return called(); }

@@ -59,6 +59,7 @@ class Stub:
         self.calls = ctypes.c_int.in_dll(self.so, "stub_calls")
         self.fail_next = ctypes.c_int.in_dll(self.so, "stub_fail_next")
         self.handle = ctypes.c_void_p.in_dll(self.so, "stub_handle")
+        self.optional = ctypes.c_void_p.in_dll(self.so, "stub_pointer")
         self.workspace = ctypes.c_size_t.in_dll(self.so, "stub_workspace")
 
     def __getattr__(self, name):
@@ -69,19 +70,20 @@ class Stub:
 def stub(module, monkeypatch):
     mod, so = module
     s = Stub(so)
-    s.calls.value, s.fail_next.value, s.workspace.value = 0, u.OK, 0
+    s.calls.value, s.fail_next.value, s.workspace.value, s.optional.value = 0, u.OK, 0, 1
     monkeypatch.setattr(u, "_calls", mod)
     monkeypatch.setattr(u, "_stream", lambda stream: 0)          # the Python path's stream
     return s
 
 
-def on_gpu(*shape, dtype=torch.bfloat16):
-    """A contiguous tensor of host memory that says it is on a GPU."""
+def on_gpu(*shape, dtype=torch.bfloat16, memory=True):
+    """A contiguous tensor of host memory that says it is on a GPU (or one without memory)."""
     n = dtype.itemsize
     for x in shape:
         n *= x
     mem = torch.zeros(max(n, 16) + 16, dtype=torch.uint8)
-    ptr = -(-mem.data_ptr() // 16) * 16
+    ptr = -(-mem.data_ptr() // 16) * 16 if memory else 0
+    n = n if memory else 0
     dev = torch.device("cuda:0")
     storage = torch._C._construct_storage_from_data_pointer(ptr, dev, n)
     stride = [1]
@@ -140,3 +142,23 @@ def test_library_error_is_raised_from_one_call(stub, monkeypatch, name):
             f()
         assert e.value.code == code and stub.calls.value == 1
         assert f() is out and stub.calls.value == 2          # the error does not stay
+
+
+@pytest.mark.parametrize("name", ["append", "append_qknorm", "step", "lse"])
+def test_storage_without_memory_goes_to_the_library_as_null(stub, name):
+    """Tables or a log-sum-exp whose storage has no memory (the typed data pointer of such a tensor
+    throws): the library gets a null pointer, as from the Python path, and says what it says of one."""
+    c = cache()
+    q, k, v, cos, sin = step_args()
+    w, out = on_gpu(H * 128), on_gpu(B, N, H, 128)
+    bare = lambda *shape: on_gpu(*shape, dtype=torch.float32, memory=False)
+    if name == "append":
+        r = c.unstep_kv_append(0, C, q, k, v, bare(N, 64), sin, q_rot=out)
+    elif name == "append_qknorm":
+        r = c.unstep_kv_append_qknorm(0, C, q, k, v, cos, bare(N, 64), w, w, q_rot=out)
+    elif name == "step":
+        r = c.unstep_step(0, C, W, q, k, v, bare(N, 64), sin, q_rot=k, out=out, use_split=False)
+    else:
+        r = c.unstep_window_attn(0, C, W, q, out=out, lse=bare(B, H, N), use_split=False)
+    assert r is out and stub.calls.value == 1
+    assert stub.optional.value is None
