@@ -213,6 +213,7 @@ class Cache:
         self._native = _calls.cache(h.value, self.B, self.H, self.T, self.k)   # None: not a plain CUDA cache
 
     def __del__(self):
+        self._native = None                # it holds the handle's address
         h = getattr(self, "handle", None)
         if h is not None and h.value:
             lib.unstep_cache_destroy(h)

@@ -162,3 +162,16 @@ def test_storage_without_memory_goes_to_the_library_as_null(stub, name):
         r = c.unstep_window_attn(0, C, W, q, out=out, lse=bare(B, H, N), use_split=False)
     assert r is out and stub.calls.value == 1
     assert stub.optional.value is None
+
+
+@pytest.mark.parametrize("name", NAMES[:4])
+def test_a_finalised_cache_is_refused(stub, name):
+    """After __del__ the handle is gone: the library is asked with a null handle, not the freed one."""
+    c = cache()
+    f, out = call(name, c)
+    assert f() is out and stub.handle.value is not None
+    c.__del__()
+    stub.calls.value = 0
+    with pytest.raises(u.UnstepError) as e:              # the Python path, the library itself
+        f()
+    assert e.value.code == u.E_NULL and stub.calls.value == 0
