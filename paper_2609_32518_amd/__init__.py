@@ -210,7 +210,11 @@ class Cache:
                                        ring_frames, self.k.data_ptr(), self.v.data_ptr()))
         self.handle = h
         self._ws: Optional[torch.Tensor] = None
-        self._native = _calls.cache(h.value, self.B, self.H, self.T, self.k)   # None: not a plain CUDA cache
+        # the native calls' view of this cache; None: not a plain CUDA cache, or a subclass with its own
+        # checks or outputs, which only the Python path asks (its scratch methods are asked by both)
+        self._native = None
+        if all(getattr(type(self), f.__name__) is f for f in _CHECK_METHODS):
+            self._native = _calls.cache(h.value, self.B, self.H, self.T, self.k, _SCRATCH_METHODS)
 
     def __del__(self):
         self._native = None                # it holds the handle's address
@@ -396,6 +400,10 @@ class Cache:
 
     def _step_workspace(self, start_frame: int, n_frames: int, window_frames: int) -> Optional[torch.Tensor]:
         return self.workspace(start_frame, n_frames, window_frames)
+
+
+_CHECK_METHODS = (Cache._strides, Cache._qkv_strides, Cache._tables, Cache._chunk_out, Cache._lse, Cache._workspace_bytes)
+_SCRATCH_METHODS = (Cache.workspace, Cache.workspace_bytes, Cache._step_workspace)
 
 
 # -- clean-cache updates (Section 3.4) ---------------------------------------------------------

@@ -35,6 +35,8 @@ struct CacheInfo {
   unstep_cache* handle;
   int64_t B, H, T;
   c10::Device device;
+  PyObject* scratch_methods;    // the tuple (Cache.workspace, Cache.workspace_bytes, Cache._step_workspace)
+  ~CacheInfo() { Py_XDECREF(scratch_methods); }
 };
 
 // A plain strided tensor on a GPU: exactly torch.Tensor or Parameter, no subclass, no functorch
@@ -211,11 +213,24 @@ bool lse_of(const CacheInfo& c, int64_t N, PyObject* o, float** p) {
   return true;
 }
 
+// Whether the scratch methods that a call would ask (`step`: _step_workspace too) are the binding's own on
+// `owner`: a subclass, or a program that replaced one, is asked through the Python path.
+bool own_scratch(const CacheInfo& c, PyObject* owner, bool step) {
+  static const char* const names[] = {"workspace", "workspace_bytes", "_step_workspace"};
+  for (int i = 0; i < (step ? 3 : 2); ++i) {
+    const Ref m{PyObject_GetAttrString(owner, names[i])};
+    if (!m.o || !PyMethod_Check(m.o) || PyMethod_GET_FUNCTION(m.o) != PyTuple_GET_ITEM(c.scratch_methods, i) ||
+        PyMethod_GET_SELF(m.o) != owner)
+      return false;
+  }
+  return true;
+}
+
 // The split-key scratch: the given tensor, or (use_split) the one the Cache object keeps as _ws,
 // replaced by a larger one when it is too small, as Cache.workspace does.  The kept tensor is held in
 // *hold until the call has been enqueued.
 bool workspace_of(const CacheInfo& c, int32_t f0, int32_t C, int32_t W, PyObject* given, PyObject* use_split, PyObject* owner,
-                  at::Tensor* hold, void** p, size_t* bytes) {
+                  bool step, at::Tensor* hold, void** p, size_t* bytes) {
   *p = nullptr;
   *bytes = 0;
   if (given != Py_None) {
@@ -226,7 +241,7 @@ bool workspace_of(const CacheInfo& c, int32_t f0, int32_t C, int32_t W, PyObject
     return true;
   }
   if (use_split == Py_False) return true;
-  if (use_split != Py_True) return false;
+  if (use_split != Py_True || !own_scratch(c, owner, step)) return false;
   size_t need = 0;
   if (unstep_attn_workspace_size(c.handle, f0, C, W, &need) != UNSTEP_OK) return false;
   if (need == 0) return true;
@@ -249,13 +264,14 @@ bool workspace_of(const CacheInfo& c, int32_t f0, int32_t C, int32_t W, PyObject
 
 // ---- functions ------------------------------------------------------------------------------------
 
-// cache(handle, B, H, T, k) -> capsule
+// cache(handle, B, H, T, k, scratch_methods) -> capsule
 PyObject* f_cache(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return guarded([&]() -> PyObject* {
-    const at::Tensor* k = n == 5 ? plain(a[4]) : nullptr;
-    if (!k) return none();
+    const at::Tensor* k = n == 6 ? plain(a[4]) : nullptr;
+    if (!k || !PyTuple_CheckExact(a[5]) || PyTuple_GET_SIZE(a[5]) != 3) return none();
     auto info = std::unique_ptr<CacheInfo>(new CacheInfo{static_cast<unstep_cache*>(PyLong_AsVoidPtr(a[0])), PyLong_AsLongLong(a[1]),
-                                                         PyLong_AsLongLong(a[2]), PyLong_AsLongLong(a[3]), k->device()});
+                                                         PyLong_AsLongLong(a[2]), PyLong_AsLongLong(a[3]), k->device(),
+                                                         (Py_INCREF(a[5]), a[5])});
     if (PyErr_Occurred()) return none();
     PyObject* cap = PyCapsule_New(info.get(), kCapsule, [](PyObject* o) {
       delete static_cast<CacheInfo*>(PyCapsule_GetPointer(o, kCapsule));
@@ -327,7 +343,7 @@ PyObject* f_window_attn(PyObject*, PyObject* const* a, Py_ssize_t n) {
     size_t bytes;
     at::Tensor made, hold;
     if (!is(q, at::kBFloat16, at::IntArrayRef(shape, 4), c->device) || !lse_of(*c, N, a[6], &lse) ||
-        !workspace_of(*c, f0, C, W, a[8], a[9], a[10], &hold, &ws, &bytes))
+        !workspace_of(*c, f0, C, W, a[8], a[9], a[10], false, &hold, &ws, &bytes))
       return none();
     const at::Tensor* out = chunk_out(*c, N, a[5], &made);
     if (!out) return none();
@@ -352,7 +368,7 @@ PyObject* f_step(PyObject*, PyObject* const* a, Py_ssize_t n) {
     size_t bytes;
     at::Tensor hold;
     if (!c || !chunk_of(*c, a + 1, false, &k) || !to_i32(a[8], &W) || !to_f64(a[12], &scale) || !lse_of(*c, k.N, a[11], &lse) ||
-        !workspace_of(*c, k.f0, k.C, W, a[13], a[14], a[15], &hold, &ws, &bytes))
+        !workspace_of(*c, k.f0, k.C, W, a[13], a[14], a[15], true, &hold, &ws, &bytes))
       return none();
     at::Tensor made_q, made;
     const at::Tensor *qr = chunk_out(*c, k.N, a[9], &made_q), *out = qr ? chunk_out(*c, k.N, a[10], &made) : nullptr;

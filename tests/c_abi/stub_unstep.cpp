@@ -9,6 +9,7 @@ int stub_calls = 0;         // calls of any entry point that would enqueue work
 int stub_fail_next = 0;     // status of the next such call; UNSTEP_OK for the others
 const void* stub_handle = nullptr;   // the handle of the last one
 const void* stub_pointer = nullptr;  // its cos or sin table if one of them is null, or its log-sum-exp
+const void* stub_scratch = nullptr;  // the scratch of the last attention or step
 size_t stub_workspace = 0;  // what unstep_attn_workspace_size reports
 
 static int called(const void* handle = nullptr, const void* p = nullptr, const void* p2 = nullptr) {
@@ -33,11 +34,13 @@ int unstep_attn_workspace_size(const unstep_cache*, int32_t, int32_t, int32_t, s
   *bytes = stub_workspace;
   return UNSTEP_OK;
 }
-int unstep_window_attn(const unstep_cache* c, int32_t, int32_t, int32_t, const void*, void*, float* lse, float, void*, size_t, void*) {
+int unstep_window_attn(const unstep_cache* c, int32_t, int32_t, int32_t, const void*, void*, float* lse, float, void* ws, size_t, void*) {
+  stub_scratch = ws;
   return called(c, lse, lse);
 }
 int unstep_step(unstep_cache* c, int32_t, int32_t, int32_t, const void*, const void*, const void*, int64_t, int64_t, const float* cos,
-                const float* sin, void*, void*, float*, float, void*, size_t, void*) {
+                const float* sin, void*, void*, float*, float, void* ws, size_t, void*) {
+  stub_scratch = ws;
   return called(c, cos, sin);
 }
 int unstep_linear(const void*, const void*, const void*, void*, int32_t, int32_t, int32_t, void*) { return called(); }

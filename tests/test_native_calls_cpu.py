@@ -12,6 +12,7 @@ import os
 import shutil
 import subprocess
 import sysconfig
+import types
 
 import pytest
 import torch
@@ -60,6 +61,7 @@ class Stub:
         self.fail_next = ctypes.c_int.in_dll(self.so, "stub_fail_next")
         self.handle = ctypes.c_void_p.in_dll(self.so, "stub_handle")
         self.optional = ctypes.c_void_p.in_dll(self.so, "stub_pointer")
+        self.scratch = ctypes.c_void_p.in_dll(self.so, "stub_scratch")
         self.workspace = ctypes.c_size_t.in_dll(self.so, "stub_workspace")
 
     def __getattr__(self, name):
@@ -95,9 +97,9 @@ def on_gpu(*shape, dtype=torch.bfloat16, memory=True):
     return t
 
 
-def cache():
+def cache(cls=u.Cache):
     shape = (B, H, (S + R) * T, 128)
-    return u.Cache(B, H, GH, GW, S, R, k_cache=on_gpu(*shape), v_cache=on_gpu(*shape))
+    return cls(B, H, GH, GW, S, R, k_cache=on_gpu(*shape), v_cache=on_gpu(*shape))
 
 
 def step_args():
@@ -175,3 +177,46 @@ def test_a_finalised_cache_is_refused(stub, name):
     with pytest.raises(u.UnstepError) as e:              # the Python path, the library itself
         f()
     assert e.value.code == u.E_NULL and stub.calls.value == 0
+
+
+@pytest.mark.parametrize("name", ["window_attn", "step"])
+@pytest.mark.parametrize("how", ["subclass", "class", "instance"])
+@pytest.mark.parametrize("method", ["workspace", "workspace_bytes", "_step_workspace", "_chunk_out"])
+def test_replaced_methods_are_asked(stub, monkeypatch, name, how, method):
+    """A subclass or a program that replaces a scratch method (or a subclass that makes its own outputs)
+    is asked on every call, as through the Python path."""
+    if method == "_chunk_out" and how != "subclass":
+        pytest.skip("a private method: subclasses only")
+    scratch, asked = on_gpu(4096, dtype=torch.uint8), []
+    own = getattr(u.Cache, method)
+
+    def mine(self, *a):
+        asked.append(method)
+        return 1024 if method == "workspace_bytes" else own(self, *a) if method == "_chunk_out" else scratch
+
+    cls = type("Own", (u.Cache,), {method: mine}) if how == "subclass" else u.Cache
+    c = cache(cls)
+    c._ws = on_gpu(2048, dtype=torch.uint8)
+    stub.workspace.value = 1024
+    if how == "class":
+        monkeypatch.setattr(u.Cache, method, mine)
+    elif how == "instance":
+        monkeypatch.setattr(c, method, mine.__get__(c), raising=False)
+    monkeypatch.setattr(u, "lib", stub)
+    f, out = call(name, c)
+    for n in (1, 2):
+        assert f() is out and stub.calls.value == n
+        if method == "_step_workspace" and name == "window_attn":
+            assert asked == []
+        else:
+            assert len(asked) >= n
+    assert stub.scratch.value == (scratch if method in ("workspace", "_step_workspace") and asked else c._ws).data_ptr()
+
+
+@pytest.mark.parametrize("name", ["window_attn", "step"])
+def test_own_scratch_methods_stay_native(stub, monkeypatch, name):
+    c = cache(type("Plain", (u.Cache,), {}))             # a subclass that replaces nothing
+    c._ws, stub.workspace.value = on_gpu(2048, dtype=torch.uint8), 1024
+    monkeypatch.setattr(u, "lib", types.SimpleNamespace(unstep_cache_destroy=u.lib.unstep_cache_destroy))  # no Python path
+    f, out = call(name, c)
+    assert f() is out and stub.calls.value == 1 and stub.scratch.value == c._ws.data_ptr()
