@@ -318,7 +318,8 @@ int unstep_svd_truncate(const float* w, int32_t rows, int32_t cols, int32_t rank
  * row-major and contiguous, on the device.  float32 accumulation and bias add, one rounding to
  * bf16 (nearest even).  One launch of the library's MFMA kernel on hip_stream: no scratch, no
  * allocation, no synchronisation.  Errors: E_NULL (x, w, y), E_SHAPE (sizes < 1, K or N not a
- * multiple of 8, more than 2^31 128 x 128 output tiles), E_ALIGN, E_HIP. */
+ * multiple of 8, more output tiles than one launch takes: 2^24 or more of 128 x 128 and, where
+ * K < 2^22, 2^23 or more of 256 x 128), E_ALIGN, E_HIP. */
 int unstep_linear(const void* x, const void* w, const void* bias, void* y, int32_t M, int32_t N, int32_t K,
                   void* hip_stream);
 

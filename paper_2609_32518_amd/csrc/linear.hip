@@ -11,20 +11,18 @@
 // fragment reads (32 rows at one chunk) hit distinct banks.  Rows past M or N read the last row
 // and are not stored.
 //
-// linear_kernel_pc (every K up to 2^22): four waves multiply, four load straight into an LDS ring; four
-// tile sizes, chosen by a cost rule in launch_linear.
+// linear_kernel_pc (every K below 2^22): four waves multiply, four load straight into an LDS ring; four
+// tile sizes, chosen by the cost rule of linear_plan.hpp.
 //
-// linear_kernel (longer rows, whose tiles 32-bit offsets cannot address): 4 waves, a 128 x 128 tile
-// of y^T, two work-groups per compute unit, wave w owning a 64 x 64 quarter as 2 x 2 blocks.  The k
-// steps are double buffered: the global loads of step s + 1 are in flight in registers while step
+// linear_kernel (longer rows, whose tiles 32-bit offsets cannot address, or outputs of which no other
+// tile fits one launch): 4 waves, a 128 x 128 tile of y^T, two work-groups per compute unit, wave w
+// owning a 64 x 64 quarter as 2 x 2 blocks.  The k steps are double buffered: the global loads of step s + 1 are in flight in registers while step
 // s is multiplied, then written to the other LDS buffer before the step's one barrier.  Chunks
 // past K read as zeros.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
-#include <cmath>
-
 #include "kernels.hpp"
+#include "linear_plan.hpp"
 
 namespace unstep {
 namespace {
@@ -32,7 +30,7 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kBM = 128;                 // x rows (columns of y^T) per work-group
 constexpr int kBN = 128;                 // W rows (columns of y) per work-group
-constexpr int kBK = 64;                  // k per step
+constexpr int kBK = kLinearBK;           // k per step
 constexpr int kRowBytes = kBK * 2;       // one tile row in LDS
 constexpr int kTileBytes = kBN * kRowBytes;
 constexpr int kChunks = kRowBytes / 16;  // 16-byte chunks per tile row
@@ -458,39 +456,25 @@ __global__ __launch_bounds__(kPCThreads, 1) void linear_kernel_pc(LinearArgs a) 
 }
 
 template <class T>
-hipError_t launch_pc(LinearArgs a, hipStream_t stream) {
-  a.tiles_m = (a.M + T::BM - 1) / T::BM;
-  a.tiles_n = (a.N + T::BN - 1) / T::BN;
+hipError_t launch_pc(const LinearArgs& a, hipStream_t stream) {
   hipLaunchKernelGGL(linear_kernel_pc<T>, dim3(unsigned(int64_t(a.tiles_m) * a.tiles_n)), dim3(kPCThreads), 0, stream, a);
   return hipGetLastError();
-}
-
-// Time of one 64-wide k step over the whole launch (us): every round of work-groups takes at least
-// `step` and the operand bytes of all tiles move at `tbps` together.
-double step_us(int32_t M, int32_t N, int bn, int bm, int slots, double step, double tbps) {
-  const double tiles = double((int64_t(N) + bn - 1) / bn) * double((int64_t(M) + bm - 1) / bm);
-  return std::max(std::ceil(tiles / slots) * step, tiles * (bn + bm) * kRowBytes / (tbps * 1e6));
 }
 
 }  // namespace
 
 hipError_t launch_linear(const uint16_t* x, const uint16_t* w, const uint16_t* bias, uint16_t* y, int32_t M,
                          int32_t N, int32_t K, hipStream_t stream) {
-  // tiles whose rows 32-bit offsets address: the direct-to-LDS kernel, with the tile size that the
-  // measured rates above put first (fixed costs of ~3 us are the same for all, so K only scales
-  // the comparison)
-  if (int64_t(256) * K * 2 < (int64_t(1) << 31)) {
-    const LinearArgs a{x, w, bias, y, M, N, K, 0, 0};
-    const double t0 = step_us(M, N, 128, 256, 256, 0.63, 12.3), t1 = step_us(M, N, 128, 128, 256, 0.31, 12.0),
-                 t2 = step_us(M, N, 64, 128, 256, 0.23, 14.5), t3 = step_us(M, N, 64, 64, 256, 0.155, 18.5);
-    const double t = std::min(std::min(t0, t1), std::min(t2, t3));
-    if (t0 == t) return launch_pc<Tile<128, 256, 3, false>>(a, stream);
-    if (t1 == t) return launch_pc<Tile<128, 128, 5, true>>(a, stream);
-    if (t2 == t) return launch_pc<Tile<64, 128, 6, true>>(a, stream);
+  const LinearTile t = linear_plan(M, N, K);
+  const LinearArgs a{x, w, bias, y, M, N, K, t.tiles_m, t.tiles_n};
+  if (!t.fits) return hipErrorInvalidConfiguration;
+  if (!t.staged) {
+    if (t.bm == 256) return launch_pc<Tile<128, 256, 3, false>>(a, stream);
+    if (t.bn == 128) return launch_pc<Tile<128, 128, 5, true>>(a, stream);
+    if (t.bm == 128) return launch_pc<Tile<64, 128, 6, true>>(a, stream);
     return launch_pc<Tile<64, 64, 5, true>>(a, stream);
   }
-  LinearArgs a{x, w, bias, y, M, N, K, (M + kBM - 1) / kBM, (N + kBN - 1) / kBN};
-  const int64_t tiles = int64_t(a.tiles_m) * a.tiles_n;
+  const int64_t tiles = int64_t(t.tiles_m) * t.tiles_n;
   hipLaunchKernelGGL(linear_kernel, dim3(unsigned(tiles)), dim3(kThreads), 0, stream, a);
   return hipGetLastError();
 }

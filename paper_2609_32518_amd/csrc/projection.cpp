@@ -28,6 +28,7 @@
 #include <vector>
 
 #include "kernels.hpp"
+#include "linear_plan.hpp"
 #include "status.hpp"
 #include "unstep.h"
 
@@ -149,8 +150,8 @@ int unstep_linear(const void* x, const void* w, const void* bias, void* y, int32
     if (!x || !w || !y) return fail(UNSTEP_E_NULL, "%s: x, w and y are required", where);
     if (M < 1 || N < 1 || K < 1) return fail(UNSTEP_E_SHAPE, "%s: M, N, K must be >= 1", where);
     if (K % 8 || N % 8) return fail(UNSTEP_E_SHAPE, "%s: K and N must be multiples of 8", where);
-    if ((int64_t(M) + 127) / 128 * ((int64_t(N) + 127) / 128) > INT32_MAX)
-      return fail(UNSTEP_E_SHAPE, "%s: too many 128 x 128 output tiles for one launch", where);
+    if (!unstep::linear_plan(M, N, K).fits)
+      return fail(UNSTEP_E_SHAPE, "%s: too many output tiles for one launch (2^32 work-items or more)", where);
     if (!aligned16(x) || !aligned16(w) || !aligned16(y) || (bias && !aligned16(bias)))
       return fail(UNSTEP_E_ALIGN, "%s: pointers must be 16-byte aligned", where);
     hipError_t e = unstep::launch_linear(static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w),
