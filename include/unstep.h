@@ -196,10 +196,11 @@ int unstep_kv_append_qknorm(unstep_cache* c, int32_t start_frame, int32_t n_fram
  *
  * workspace (optional): device scratch for splitting the key range over several
  * work-groups; unstep_attn_workspace_size gives the bytes used for this call.  With
- * workspace == NULL or workspace_bytes smaller than that, the call runs unsplit (same
- * results up to fp32 summation order, possibly slower).  The size depends only on the
- * shapes (batch, heads, chunk tokens, retained key count), not on what is stored, so it
- * can be queried before the chunk is appended.
+ * workspace_bytes smaller than that, the call is split over fewer work-groups or runs unsplit,
+ * with workspace == NULL it runs unsplit (same results up to fp32 summation order, possibly
+ * slower).  The size depends only on the shapes (batch, heads, chunk tokens, retained key
+ * count), not on what is stored, so it can be queried before the chunk is appended; a wider
+ * window can need a little less than a narrower one.
  * Errors: those of unstep_window_segments, plus E_NULL (q_rot, out), E_SHAPE (batch * heads *
  * ceil(N / 256) >= 2^23 query tiles), E_ALIGN, E_HIP;
  * unstep_attn_workspace_size: E_NULL, E_SHAPE, E_RANGE (argument checks only). */

@@ -133,9 +133,9 @@ int plan_attn(const unstep_cache* c, const unstep::CacheIndex& idx, int32_t f0, 
   }
   a->seg_l0[UNSTEP_MAX_SEGMENTS] = INT32_MAX;
   a->scale = scale > 0.f ? scale : 1.0f / std::sqrt(float(UNSTEP_HEAD_DIM));
-  const unstep::AttnPlan plan = unstep::attn_plan(c->B, c->H, N, a->n_keys);
+  const unstep::AttnPlan plan = unstep::attn_plan(c->B, c->H, N, a->n_keys, workspace ? ws_bytes : 0);
   a->parts = 1;
-  if (plan.workspace > 0 && workspace && ws_bytes >= plan.workspace) {
+  if (plan.workspace > 0) {
     a->groups = plan.groups;
     a->parts = plan.parts;
     a->part_o = static_cast<float*>(workspace);

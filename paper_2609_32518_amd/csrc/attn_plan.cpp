@@ -23,7 +23,7 @@ double contiguous_us(int64_t units, int64_t groups) { return 1.82 * double(units
 
 }  // namespace
 
-AttnPlan attn_plan(int32_t B, int32_t H, int32_t N, int32_t n_keys) {
+AttnPlan attn_plan(int32_t B, int32_t H, int32_t N, int32_t n_keys, size_t scratch) {
   constexpr int64_t kSlots = kAttnMaxGroups;
   const int64_t qtiles = int64_t(B) * H * ((N + kAttnBlockQ - 1) / kAttnBlockQ);
   const int64_t tk = (n_keys + kAttnBlockK - 1) / kAttnBlockK;
@@ -40,7 +40,7 @@ AttnPlan attn_plan(int32_t B, int32_t H, int32_t N, int32_t n_keys) {
     if (g <= qtiles) return plain;
     const double t_plain = double((qtiles + kSlots - 1) / kSlots) * double(tk) * 1.66;
     const double t_bal = double((units + g - 1) / g) * 1.82 + double(attn_workspace_bytes(int32_t(g))) / 4.5e6 + 2.0;
-    return t_bal < t_plain ? balanced(g, qtiles) : plain;
+    return t_bal < t_plain && attn_workspace_bytes(int32_t(g)) <= scratch ? balanced(g, qtiles) : plain;
   }
   // Few query tiles: every tile cut into the same number of equal parts of at least four key tiles,
   // so that each work-group walks one segment (one pipeline fill, one partial): as many parts as
@@ -52,14 +52,18 @@ AttnPlan attn_plan(int32_t B, int32_t H, int32_t N, int32_t n_keys) {
   // contiguously over 256 work-groups), [324, 4544] of 12 heads 30.0 in 9 (84.6, 34.6), [300, 1200]
   // of 8 heads 21.0 in 4 (28.1, 28.5), [256, 25600] of 2 heads 27.6 in 100 (432), and [300, 500] of
   // 8 heads 16.3 whole (18.3 in 2).
-  int64_t parts = std::max<int64_t>(1, std::min(kSlots / qtiles, tk / 4));
+  // The part count falls now and then as the window grows, so a scratch sized once for the widest
+  // window can hold fewer parts than a narrower one wants: it then gets as many as fit (a scratch that
+  // holds the parts of the full plan gives that plan).
+  const int64_t fit = std::min<int64_t>(kSlots, int64_t(scratch / attn_workspace_bytes(1)));
+  int64_t parts = std::max<int64_t>(1, std::min(fit / qtiles, tk / 4));
   const int64_t longest = (tk + parts - 1) / parts;
   parts = (tk + longest - 1) / longest;
   const double merge = 4.5 + 0.75 * double(parts) / attn_merge_slices(int32_t(qtiles), int32_t(parts));
   if (parts > 1 && double(tk - longest) * 1.25 < merge) parts = 1;
   const double tile = std::max(1.08, 0.55 + 0.0044 * double(parts * qtiles));
   const double t_parts = 8.0 + double(longest) * tile + merge;
-  if (parts > 1 && g == kSlots && contiguous_us(units, g) < t_parts) return balanced(g, qtiles);
+  if (parts > 1 && g == kSlots && fit >= g && contiguous_us(units, g) < t_parts) return balanced(g, qtiles);
   return parts > 1 ? balanced(parts * qtiles, qtiles) : plain;
 }
 

@@ -110,8 +110,6 @@ inline int attn_merge_slices(int32_t query_tiles, int32_t parts) {
   return s;
 }
 
-AttnPlan attn_plan(int32_t B, int32_t H, int32_t N, int32_t n_keys);
-
 // Scratch of a balanced launch: two partial-output slots of 256 rows x 128 fp32 per
 // work-group, then their (exponent offset, row sum) pairs.
 constexpr size_t attn_workspace_bytes(int32_t groups) {
@@ -119,6 +117,9 @@ constexpr size_t attn_workspace_bytes(int32_t groups) {
 }
 // The most any launch needs (kAttnMaxGroups work-groups).
 constexpr size_t kAttnMaxWorkspace = attn_workspace_bytes(kAttnMaxGroups);
+
+// The plan whose partials fit `scratch` bytes.
+AttnPlan attn_plan(int32_t B, int32_t H, int32_t N, int32_t n_keys, size_t scratch = kAttnMaxWorkspace);
 
 hipError_t launch_window_attn(const AttnArgs& a, hipStream_t stream);
 

@@ -23,6 +23,7 @@
 //   step f0 C W split          (unstep_step; split: pass a large enough workspace)
 //   attn f0 C W split          (unstep_window_attn)
 //   noalloc f0 C W             (unstep_window_attn_noalloc)
+//   scratch f0 C W bytes       (unstep_window_attn with that much scratch)
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -246,18 +247,23 @@ int main() {
       } else {
         rc = unstep_cache_advance(c, f0, C);
       }
-    } else if (op == "step" || op == "attn" || op == "noalloc") {
+    } else if (op == "step" || op == "attn" || op == "noalloc" || op == "scratch") {
       int32_t f0, C, W, split = 0;
-      in >> f0 >> C >> W;
-      if (op != "noalloc") in >> split;
       size_t ws = 0;
-      if (split && c) unstep_attn_workspace_size(c, f0, C, W, &ws);
+      in >> f0 >> C >> W;
+      if (op == "scratch") {
+        in >> ws;
+        split = 1;
+      } else if (op != "noalloc") {
+        in >> split;
+        if (split && c) unstep_attn_workspace_size(c, f0, C, W, &ws);
+      }
       void* wsp = split && ws ? fake(8) : nullptr;
       if (op == "step")
         rc = unstep_step(c, f0, C, W, fake(2), fake(3), fake(4), int64_t(H) * UNSTEP_HEAD_DIM, UNSTEP_HEAD_DIM,
                          (const float*)fake(5),
                          (const float*)fake(6), fake(7), fake(9), nullptr, 0.f, wsp, ws, nullptr);
-      else if (op == "attn")
+      else if (op == "attn" || op == "scratch")
         rc = unstep_window_attn(c, f0, C, W, fake(7), fake(9), nullptr, 0.f, wsp, ws, nullptr);
       else
         rc = unstep_window_attn_noalloc(c, f0, C, W, fake(7), fake(9), nullptr, 0.f, nullptr);

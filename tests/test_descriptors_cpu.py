@@ -171,3 +171,40 @@ def test_benchmark_workloads_match_the_oracle(driver, name):
         r.attn(wl.f0, wl.C, wl.W, "noalloc")
     out = run(driver, r.script)
     r.check(out, name)
+
+
+@pytest.mark.parametrize("H,gh,gw,C", [(1, 10, 10, 1), (2, 10, 10, 3), (12, 18, 18, 1), (24, 13, 15, 2), (5, 16, 17, 1), (3, 4, 6, 3)])
+def test_a_scratch_sized_once_serves_every_window(driver, H, gh, gw, C):
+    """A scratch of the bytes that the widest window of a chunk uses: a narrower window that would be split
+    with its own scratch is split with this one (into as many parts as fit, partials inside it)."""
+    R = 24
+    r = Replay(1, H, gh, gw, 0, R)
+    r.append(0, R - C, advance=True)
+    r.append(R - C, C)
+    f0 = R - C
+    for W in range(R - C + 1):                                   # what each window asks for
+        r.attn(f0, C, W, "attn", split=True)
+    out = run(driver, r.script)
+    r.check(out, "own scratch")
+    own = [o["attn"][0] for o in out[-(R - C + 1):]]
+    per_group = 2 * 256 * 130 * 4
+    split = 0
+    for widest in range(R - C + 1):
+        have = own[widest]["groups"] if own[widest]["split"] else 0
+        for W in range(widest + 1):
+            r.script.append(f"scratch {f0} {C} {W} {have * per_group}")
+            r.expect.append(dict(rc=0, append=[], attn=[r.o.key_rows(f0, C, W).tolist()]))
+    out = run(driver, r.script)
+    r.check(out, "one scratch")
+    got = iter([o["attn"][0] for o in out[-(R - C + 1) * (R - C + 2) // 2:]])
+    for widest in range(R - C + 1):
+        have = own[widest]["groups"] if own[widest]["split"] else 0
+        for W in range(widest + 1):
+            g = next(got)
+            assert not g["split"] or g["groups"] <= have, (widest, W)
+            if own[W]["split"] and have:
+                split += 1
+                assert g["split"], (widest, W, own[W]["groups"], have)
+                if own[W]["groups"] <= have:
+                    assert g["groups"] == own[W]["groups"], (widest, W)
+    assert split or (H, gh) == (3, 4)
