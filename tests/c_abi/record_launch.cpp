@@ -11,8 +11,10 @@
 //   attention: for every (batch, head, query tile), the row the K loader and the V loader fetch
 //   for every retained key, walking each work-group's segments and loader cursors in the
 //   kernel's tile order; plus checks that the segments of every query tile cover its keys
-//   exactly once, that K and V rows agree, that every row lies inside the cache, and that the
-//   merge reads only partials some work-group wrote.
+//   exactly once, that K and V rows agree, that every row lies inside the cache, that the
+//   merge reads only partials some work-group wrote, and, for a launch that names a whole number of
+//   work-groups per query tile, that the one-segment lookup and the merge's owners by that number
+//   say the same.
 // The Python side (tests/test_descriptors_cpu.py) compares these rows with the oracle's slot
 // map and key rows.
 //
@@ -137,12 +139,18 @@ std::string describe_attn(const AttnArgs& a) {
   std::vector<std::vector<int>> wrote(n_tiles);       // partial slot written by each group, per tile
   std::vector<std::vector<int64_t>> writer(n_tiles);
   bool rows_in_bounds = true, kv_agree = true, tail_ok = true, fast_ok = true;
+  // parts: named where it applies (0 only where the groups are no whole number per tile)
+  bool parts_ok = a.parts ? sc.G == int64_t(a.parts) * n_tiles : sc.G % n_tiles != 0;
   int64_t segments = 0;
   for (int64_t g = 0; g < sc.G; ++g) {
     const int64_t u_begin = sc.start(g);
     for (int64_t u_hi = sc.start(g + 1); u_hi > u_begin;) {
       const unstep::Segment s = unstep::take_segment(sc, u_begin, u_hi);
       ++segments;
+      if (a.parts) {
+        const unstep::Segment p = unstep::part_segment(sc.Tk, a.parts, int32_t(g));
+        parts_ok = parts_ok && p.t == s.t && p.k0 == s.k0 && p.k1 == s.k1 && p.slot == s.slot && p.full == s.full && u_hi == u_begin;
+      }
       const int32_t k_begin = s.k0 * kK;
       const int32_t k_end = a.n_keys < s.k1 * kK ? a.n_keys : s.k1 * kK;
       const int32_t n = (k_end - k_begin + kK - 1) / kK;
@@ -190,6 +198,7 @@ std::string describe_attn(const AttnArgs& a) {
     // a query tile cut between work-groups: the merge reads the partial of every group from its
     // first owner to its last, in slot 0 if the group's range starts inside the tile, else 1
     const int64_t ua = t * sc.Tk, ga = sc.owner(ua), gb = sc.owner(ua + sc.Tk - 1);
+    if (a.parts) parts_ok = parts_ok && ga == t * a.parts && gb == ga + a.parts - 1 && sc.start(ga) >= ua;
     if (ga == gb) {
       merge_ok = merge_ok && wrote[t].empty();
       continue;
@@ -211,7 +220,7 @@ std::string describe_attn(const AttnArgs& a) {
                     ",\"rows_in_bounds\":" + (rows_in_bounds ? "true" : "false") +
                     ",\"tail_rows_ok\":" + (tail_ok ? "true" : "false") +
                     ",\"merge_reads_written\":" + (merge_ok ? "true" : "false") +
-                    ",\"single_run_tiles_ok\":" + (fast_ok ? "true" : "false") + ",\"rows\":" + ints(rows0) + "}";
+                    ",\"parts_ok\":" + (parts_ok ? "true" : "false") + ",\"single_run_tiles_ok\":" + (fast_ok ? "true" : "false") + ",\"rows\":" + ints(rows0) + "}";
   return out;
 }
 

@@ -8,7 +8,7 @@ split, the rotary tables) with launchers that record the kernel descriptors inst
 launching them.  For each call it reports the slot every appended frame is written to and, for
 attention, the cache row the K and V loaders fetch for every retained key of every query tile,
 computed with the kernels' own address arithmetic (seg_table.hpp) over each work-group's
-segments and loader cursors, plus coverage, bounds and merge checks.  Here those rows must equal
+segments and loader cursors, plus coverage, bounds, merge and parts checks.  Here those rows must equal
 the oracle's slot map and key rows, call by call, over the seeded random call sequences of the
 GPU suite and the benchmark workloads.  No GPU is used.
 """
@@ -113,7 +113,7 @@ class Replay:
             assert len(got["attn"]) == len(want["attn"]), where
             for a, rows in zip(got["attn"], want["attn"]):
                 for flag in ("covered_once", "k_v_agree", "same_rows_every_tile", "rows_in_bounds", "tail_rows_ok",
-                             "merge_reads_written", "single_run_tiles_ok"):
+                             "merge_reads_written", "parts_ok", "single_run_tiles_ok"):
                     assert a[flag], (where, flag)
                 assert a["n_keys"] == len(rows), where
                 # the launch walks the retained rows in ascending cache order (attention over
