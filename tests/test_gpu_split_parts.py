@@ -1,7 +1,7 @@
-"""Attention split into every number of parts the plan makes, against the float64 oracle: query
-tiles cut into 1, 2, 4, 5, 8 and 9 parts (the merge loads four partials at a time), parts of one or
-two key tiles, a ragged last query tile whose merge blocks past the chunk return at once, and the
-contiguous split whose work-groups walk the ends of two query tiles."""
+"""Attention split into the kinds of parts the plan makes, against the float64 oracle: query tiles
+whole and cut into 3, 4, 5, 9, 11 and 21 parts of four and more key tiles (the merge loads four partials at
+a time, in one, two, four or eight slices), a ragged last query tile whose merge blocks past the chunk
+return at once, and the contiguous split whose work-groups walk the ends of two query tiles."""
 import numpy as np
 import pytest
 import torch

@@ -7,6 +7,8 @@ import subprocess
 
 import pytest
 
+from tests.test_gpu_linear_exact import SHAPES
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 SOURCE = r"""
@@ -55,3 +57,10 @@ def test_largest_outputs_fit_one_launch(plan):
         if fits:
             assert tn * tm * threads < 2 ** 32, (M, N, K, bn, bm, staged)
     assert plan([(2 ** 30, 8, 8)])[0][5] and plan([(2 ** 30, 64, 40)])[0][5]
+
+
+def test_tiles_of_the_exact_cases(plan):
+    """The sizes that the GPU test of whole numbers names reach every tile and the staged kernel."""
+    got = plan([s[:3] for s in SHAPES])
+    assert [(bn, bm, bool(staged)) for bn, bm, staged, *_ in got] == [s[3] for s in SHAPES]
+    assert {s[3] for s in SHAPES} == {(128, 256, False), (128, 128, False), (64, 128, False), (64, 64, False), (128, 128, True)}
