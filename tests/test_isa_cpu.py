@@ -5,10 +5,13 @@ v_readlane, a compare into an SGPR pair) needs 5 wait states between the two on 
 with fewer, the load may take the register's previous contents as its address.  The compiler
 inserts those wait states before the memory instructions it generates itself, but it does not
 know what an inline-assembly string does, so nothing guarantees them before the attention and
-projection kernels' `global_load_lds_dwordx4`.  This test compiles both sources exactly as the
-build does and checks every such load: within the 5 wait states before it (each instruction one,
-`s_nop n` n + 1) no VALU instruction writes an SGPR of its scalar base, and that window does not
-start in another basic block (where the predecessor's last instructions could not be checked).
+projection kernels' `global_load_lds_dwordx4` and `buffer_load_dwordx4 ... lds`.  A load into LDS
+also reads M0, which needs one wait state after a scalar write (and is taken to need 5 after a
+VALU write).  This test compiles both sources exactly as the build does and checks every such load:
+within the 5 wait states before it (each instruction one, `s_nop n` n + 1) no VALU instruction
+writes an SGPR of its scalar base or descriptor or M0, the instruction right before it writes no M0, and
+that window does not start in another basic block (where the predecessor's last instructions could
+not be checked).
 CPU only: hipcc cross-compiles for gfx950 without a GPU.
 """
 import importlib.util
@@ -64,12 +67,16 @@ def _valu_sgpr_writes(words) -> set:
     return out
 
 
+# a load of either kind into LDS: its address register(s) and its scalar base or descriptor
+_LOAD = re.compile(r"(?:global_load_lds_dwordx4\s+v\d+,\s*|buffer_load_dwordx4\s+v\d+,\s*(?=.*\blds\b))(s\[\d+:\d+\])")
+
+
 def scan(asm: str):
     """(loads, problems): problems lists the loads whose base may be read too early."""
     lines = asm.splitlines()
     loads, problems = 0, []
     for i, line in enumerate(lines):
-        m = re.search(r"global_load_lds_dwordx4\s+v\d+,\s*(s\[\d+:\d+\])", line)
+        m = _LOAD.search(line)
         if not m:
             continue
         loads += 1
@@ -83,6 +90,9 @@ def scan(asm: str):
                 problems.append(f"line {i + 1}: only {waits} wait states in its block before the load")
                 break
             words = t.replace(",", " ").split()
+            if len(words) > 1 and words[1] == "m0" and (words[0].startswith("v_") or waits < 1):
+                problems.append(f"line {i + 1}: M0 written by `{t}` {waits} wait states before")
+                break
             if words[0].startswith("v_") and _valu_sgpr_writes(words) & base:
                 problems.append(f"line {i + 1}: base {m.group(1)} written by `{t}` {waits} wait states before")
                 break
@@ -106,12 +116,25 @@ def test_scan_finds_a_planted_hazard():
     assert scan(other) == (1, [])
     carry = planted.replace("\tv_readfirstlane_b32 s2, v4", "\tv_add_co_u32_e64 v9, s[2:3], v4, v5")
     assert len(scan(carry)[1]) == 1
+    for reg, n in (("s_mov_b32 m0, s7", 0), ("s_add_u32 m0, s7, s8", 0), ("v_readfirstlane_b32 m0, v3", 3)):
+        m0 = fixed.replace("\t;;#ASMSTART\n\ts_nop 4", f"\ts_nop 4\n\t{reg}\n" + "\ts_nop 0\n" * n + "\t;;#ASMSTART")
+        assert len(scan(m0)[1]) == 1, m0
+        more = m0.replace("\t;;#ASMSTART", ("\ts_nop 0\n" if n == 0 else "\ts_nop 1\n") + "\t;;#ASMSTART")
+        assert scan(more) == (1, []), more
+    buffer = planted.replace("global_load_lds_dwordx4 v1, s[2:3]", "buffer_load_dwordx4 v1, s[0:3], 0 offen lds")
+    assert len(scan(buffer)[1]) == 1
+    assert scan(buffer.replace("\t;;#ASMSTART", "\t;;#ASMSTART\n\ts_nop 4")) == (1, [])
+    assert scan(buffer.replace("offen lds", "offen")) == (0, [])       # an ordinary load, the compiler's own
     at_block_start = "\n".join(["k:", "\tglobal_load_lds_dwordx4 v1, s[2:3]"])
     assert len(scan(at_block_start)[1]) == 1
 
 
 @pytest.mark.parametrize("source", ["window_attn.hip", "linear.hip"])
 def test_inline_asm_loads_read_no_freshly_written_sgpr(source):
-    loads, problems = scan(_assembly(source))
+    asm = _assembly(source)
+    loads, problems = scan(asm)
     assert loads > 0, "no direct-to-LDS load found: the scan no longer matches the kernel"
+    # every load of either mnemonic into LDS was recognised
+    assert loads == len(re.findall(r"^\s*(?:global_load_lds_|buffer_load_\w+\s.*\blds\b)", asm, re.M))
+    assert source != "linear.hip" or "buffer_load_dwordx4" in asm
     assert not problems, "\n".join(problems[:20])
