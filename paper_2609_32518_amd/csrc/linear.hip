@@ -222,7 +222,7 @@ struct Tile {
   static constexpr int YPitch = BN * 2 + 16;               // y staging rows
   static constexpr int Lds = St * Stage;
   static_assert(BM * YPitch <= Lds && Lds <= 160 * 1024, "LDS");
-  static_assert((St - 3) * Loads < 63, "vmcnt range");
+  static_assert((St - 2) * Loads <= 63, "vmcnt range: a prologue waits with St - 2 stages in flight");
 };
 
 // Workgroup barrier; at most kLeft of this wave's LDS reads are still in flight.
