@@ -47,3 +47,30 @@ def test_parts(B, H, gh, gw, C, S, W, parts):
         want, want_lse = m.expected(ref, f, C, W)
         check_attention(host(out), want, f"parts {f}")
         assert np.max(np.abs(lse.cpu().numpy() - want_lse)) <= LSE_ABS
+
+
+@pytest.mark.parametrize("groups,parts", [(216, 9), (215, 8), (72, 3), (71, 2), (47, 1), (1, 1)])
+def test_scratch_for_some_of_the_parts(groups, parts):
+    """A scratch of fewer work-groups than the plan's 9 parts of 24 query tiles: as many parts as it holds,
+    and nothing written past it."""
+    import paper_2609_32518_amd as u
+
+    log(f"parts: scratch of {groups} work-groups -> {parts}")
+    C, W = 1, 12
+    m = Mirror(u, 1, 12, 6, 54, 1, W + C + 1, guard_rows=64)
+    f0 = W + 2
+    for f in range(f0):
+        m.append(f, C, (33, f))
+    ws = torch.full((groups * ROWS + 4096,), 0x5a, dtype=torch.uint8, device="cuda")
+    q_rot, _, _, ref = m.step(f0, C, W, (33, 100))
+    lse = torch.empty((1, 12, C * m.T), device="cuda")
+    out = m.lib.unstep_window_attn(f0, C, W, q_rot, lse=lse, workspace=ws[:groups * ROWS])
+    torch.cuda.synchronize()
+    assert bool((ws[groups * ROWS:] == 0x5a).all())
+    assert bool((ws == 0x5a).all()) == (parts == 1)
+    # the last work-group's partial outputs: written by the last of parts * 24 work-groups, none after it
+    o = ws[:parts * 24 * 2 * 256 * 128 * 4].view(-1, 2 * 256 * 128 * 4)[-1] if parts > 1 else ws[:0]
+    assert parts == 1 or not bool((o == 0x5a).all())
+    want, want_lse = m.expected(ref, f0, C, W)
+    check_attention(host(out), want, f"scratch of {groups}")
+    assert np.max(np.abs(lse.cpu().numpy() - want_lse)) <= LSE_ABS
