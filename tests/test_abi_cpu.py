@@ -320,6 +320,15 @@ def test_schedule_choice_follows_the_measured_costs():
     assert ws(0, 21, 18, 3, 18) > 0                # unwindowed, 32,760 keys
     assert ws(0, 12, 20, 1, 11) > 0                # one-frame chunk over 12 frames
 
+    # many query tiles over few key tiles: the partials' merge costs more than shorter ranges save, so
+    # they stay whole (24 heads of [540 queries, 720 keys]: 21.1 us, 26.7 in 3 parts; 40 of [540, 1080]
+    # 27.6 and 30.3 in 2; 30 of [1024, 1024] 26.6 and 31.7), longer ranges are split
+    assert ws(0, 8, 1, 3, 1, H=24, gh=9, gw=20) == 0
+    assert ws(0, 8, 3, 3, 3, H=40, gh=9, gw=20) == 0
+    assert ws(0, 8, 0, 4, 0, H=30, gh=16, gw=16) == 0
+    assert ws(0, 16, 12, 3, 12, H=24, gh=9, gw=20) > 0
+    assert ws(0, 16, 12, 3, 12, H=40, gh=9, gw=20) > 0
+
     def part_bytes(groups):                          # two fp32 partials (o, offset, sum) per work-group
         return groups * 2 * 256 * (128 + 2) * 4
     # 84 query tiles: 3 work-groups per tile (252 of 256 units), each walks a third of a tile

@@ -201,7 +201,7 @@ def test_a_scratch_sized_once_serves_every_window(driver, H, gh, gw, C):
         have = own[widest]["groups"] if own[widest]["split"] else 0
         for W in range(widest + 1):
             g = next(got)
-            assert not g["split"] or g["groups"] <= have, (widest, W)
+            assert not g["split"] or own[W]["split"] and g["groups"] <= have, (widest, W)
             if own[W]["split"] and have:
                 split += 1
                 assert g["split"], (widest, W, own[W]["groups"], have)
