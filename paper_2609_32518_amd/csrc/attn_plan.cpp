@@ -18,9 +18,13 @@ AttnPlan balanced(int64_t groups, int64_t qtiles) {
                   size_t(groups) * 2 * kAttnBlockQ * kHeadDim, groups % qtiles == 0 ? int32_t(groups / qtiles) : 0};
 }
 
-// Two ends of segments per work-group: units of ~1.82 us plus ~20 us of fill, partials and merge (12
-// heads: [1560 queries, 18720 keys] 183 us at 96 units each, [1800, 9000] 62 us at 22).
-double contiguous_us(int64_t units, int64_t groups) { return 1.82 * double(units) / double(groups) + 20.0; }
+// Times (us) of long ranges of 50-128 query tiles, split contiguously over 256 work-groups (two ends of
+// segments each) and into equal parts on `groups` work-groups, of which fewer draw less power and run
+// faster: fitted to 79 shapes, on which the choice between the two is within 1% of the better one
+// (96 query tiles, 2 parts on 192 work-groups: [1015 queries, 6100 keys] 81 in parts, 85 contiguous;
+// [1002, 16000] 184 and 181; [3852, 21900] 235 and 227).
+double contiguous_us(int64_t units) { return 23.8 + 1.63 * double(units) / kAttnMaxGroups; }
+double parts_us(int64_t longest, int64_t groups) { return 16.9 + double(longest) * (0.483 + 0.00423 * double(groups)); }
 
 // The plan with at most `slots` work-groups when it splits.
 AttnPlan plan_of(int32_t B, int32_t H, int32_t N, int32_t n_keys, int64_t slots) {
@@ -60,11 +64,8 @@ AttnPlan plan_of(int32_t B, int32_t H, int32_t N, int32_t n_keys, int64_t slots)
   parts = (tk + longest - 1) / longest;
   const double partial_mb = double(B) * H * N * double(parts) * (kHeadDim + 2) * 4e-6;
   if (parts > 1 && double(tk - longest) * 1.1 < 2.5 + 2.4 * std::sqrt(partial_mb)) parts = 1;
-  // against the contiguous split (long ranges): the merge adds 4.5 plus up to 0.75 per part
-  const double merge = 4.5 + 0.75 * double(parts) / attn_merge_slices(int32_t(qtiles), int32_t(parts));
-  const double tile = std::max(1.08, 0.55 + 0.0044 * double(parts * qtiles));
-  const double t_parts = 8.0 + double(longest) * tile + merge;
-  if (parts > 1 && g == kSlots && slots >= g && contiguous_us(units, g) < t_parts) return balanced(g, qtiles);
+  if (parts > 1 && g == kSlots && slots >= g && contiguous_us(units) < parts_us(longest, parts * qtiles))
+    return balanced(g, qtiles);
   return parts > 1 ? balanced(parts * qtiles, qtiles) : plain;
 }
 

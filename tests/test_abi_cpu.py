@@ -333,6 +333,11 @@ def test_schedule_choice_follows_the_measured_costs():
         return groups * 2 * 256 * (128 + 2) * 4
     # 84 query tiles: 3 work-groups per tile (252 of 256 units), each walks a third of a tile
     assert ws(0, 12, 20, 1, 11) == part_bytes(252)
+    # 96 query tiles leave 64 of 256 work-groups without a part of two each: long ranges go contiguously
+    # over all of them (96 tiles of [1002 queries, 16000 keys]: 181 us, 184 in 2 parts), shorter ones do
+    # not ([1015, 6100]: 85 and 81)
+    assert ws(0, 32, 27, 3, 27, H=12, gh=20, gw=32) == part_bytes(256)
+    assert ws(0, 32, 27, 3, 7, H=12, gh=20, gw=32) == part_bytes(192)
     # 2 query tiles of 400 key tiles: 128 work-groups per tile would get 3 units each, so the
     # split stays at units / 4 = 200 (no work-group under 4 units, none empty)
     assert ws(0, 101, 100, 1, 99, H=2, gh=16, gw=16) == part_bytes(200)
