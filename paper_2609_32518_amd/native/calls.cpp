@@ -215,10 +215,10 @@ bool lse_of(const CacheInfo& c, int64_t N, PyObject* o, float** p) {
 
 // Whether the scratch methods that a call would ask (`step`: _step_workspace too) are the binding's own on
 // `owner`: a subclass, or a program that replaced one, is asked through the Python path.
+PyObject* scratch_names[3];    // interned, made with the module
 bool own_scratch(const CacheInfo& c, PyObject* owner, bool step) {
-  static const char* const names[] = {"workspace", "workspace_bytes", "_step_workspace"};
   for (int i = 0; i < (step ? 3 : 2); ++i) {
-    const Ref m{PyObject_GetAttrString(owner, names[i])};
+    const Ref m{PyObject_GetAttr(owner, scratch_names[i])};
     if (!m.o || !PyMethod_Check(m.o) || PyMethod_GET_FUNCTION(m.o) != PyTuple_GET_ITEM(c.scratch_methods, i) ||
         PyMethod_GET_SELF(m.o) != owner)
       return false;
@@ -453,4 +453,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, methods, nul
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__calls() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__calls() {
+  const char* const names[3] = {"workspace", "workspace_bytes", "_step_workspace"};
+  for (int i = 0; i < 3; ++i)
+    if (!(scratch_names[i] = PyUnicode_InternFromString(names[i]))) return nullptr;
+  return PyModule_Create(&module);
+}
