@@ -36,13 +36,11 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("B,H,gh,gw,C,S,W,R,f0,parts,runs,needles", CASES)
-@pytest.mark.parametrize("use_split", [True, False])
+@pytest.mark.parametrize("B,H,gh,gw,C,S,W,R,f0,parts,runs,needles,use_split",
+                         [c + (True,) for c in CASES] + [CASES[3] + (False,)])      # the others are too long whole
 def test_rewalk_short(B, H, gh, gw, C, S, W, R, f0, parts, runs, needles, use_split):
     import paper_2609_32518_amd as u
 
-    if not use_split and (parts == 1 or (min(S, f0) + W + C) * gh * gw > 64 * SHORT):
-        pytest.skip("the same launch, or a range that the general kernel walks")
     log(f"rewalk short: B {B} H {H} grid {gh}x{gw} C {C} S {S} W {W} R {R} f0 {f0} parts {parts} split {use_split}")
     m = Mirror(u, B, H, gh, gw, S, R, guard_rows=64)
     for f in range(0, f0, C):
