@@ -626,7 +626,8 @@ __global__ __launch_bounds__(kThreads) void window_attn_kernel(AttnArgs a) {
 // rescales the sums by 2^((M_old - M) c2) when it raises M and adds w = l 2^((m - M) c2),
 // out = sum w o / sum w.
 // A [390 queries, 3315 keys] call of 24 heads (5 parts): 8.5 us before, 5.7 so; one frame of 1560
-// queries over 18720 keys (12 heads, 3 parts): 10.2 and 8.4.
+// queries over 18720 keys (12 heads, 3 parts): 10.2 and 8.3 with other work between the calls, 7.3 on
+// average over a stream of such frames.
 // What bounds it: the latency of the partials' loads, one after the other, and (all but the largest
 // launches) the launch itself.  So the loads of four partials are in flight together, a tile cut into
 // many parts has them merged in kSlices slices side by side (slice s takes partials s, s + kSlices,
