@@ -22,7 +22,8 @@ SHAPES = [
     (1365, 1000, 1032), (1281, 1024, 320),
     # 64 x 64: one value more and less than a tile, the smallest call, deep k
     (65, 72, 8), (63, 64, 64), (1, 8, 8), (64, 136, 4104), (129, 3072, 200),
-    # rows longer than the tiles' 32-bit offsets address: the register-staged kernel
+    # rows longer than the tiles' 32-bit offsets address: the register-staged kernel (the bound is wider
+    # than the values there; test_gpu_linear_exact.py checks those)
     (2, 8, (1 << 22) + 8),
 ]
 
