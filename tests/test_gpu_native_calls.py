@@ -137,3 +137,29 @@ def test_other_forms_still_run_and_refusals_still_raise():
         u.unstep_emit(x, x, 1.5)
     torch.cuda.synchronize()
     assert c.frame_map()[1] == F0 + C - 1
+
+
+@pytest.mark.parametrize("name", ["renoise", "emit"])
+def test_update_in_place_is_applied_once_with_an_error_pending(name):
+    """A HIP error that something else left on this thread is reported by the next launch, whose kernel has
+    been enqueued: the call says so and does not enqueue it again."""
+    import ctypes
+
+    u = _u()
+    f = getattr(u, f"unstep_{name}")
+    x, y = (torch.randn(4096, device="cuda").bfloat16() for _ in range(2))
+    once = f(x, y, 0.5)
+    torch.cuda.synchronize()
+    with open("/proc/self/maps") as maps:
+        path = next(l.split()[-1] for l in maps if "libamdhip64" in l)
+    hip, p = ctypes.CDLL(path), ctypes.c_void_p()
+    assert hip.hipMalloc(ctypes.byref(p), ctypes.c_size_t(1 << 60)) != 0         # more than any device has
+    try:
+        with pytest.raises(u.UnstepError) as e:
+            f(x, y, 0.5, out=x)
+        assert e.value.code == u.E_HIP
+    finally:
+        hip.hipGetLastError()                                                   # leaves none behind
+    torch.cuda.synchronize()
+    _same(x, once)
+    _same(f(x, y, 0.5, out=x), f(once, y, 0.5))
